@@ -5,6 +5,7 @@
 // float32 operands (small fp32 models) run on a register-blocked VALU kernel with
 // the same epilogues.
 #include "gemm_kernel.h"
+#include "gemm_pingpong.h"
 
 namespace tadm {
 namespace {
@@ -14,6 +15,9 @@ namespace {
 template <class T>
 struct Epi<EPI_STORE, T> {
   static constexpr bool kGlu = false;
+  static constexpr bool kRow = true;
+  __device__ static T* out_row(const EpiParams& e, int m) { return static_cast<T*>(e.out) + (size_t)m * e.ldo; }
+  __device__ static f32x4 row_out(f32x4 v) { return v; }
   __device__ static void apply(const EpiParams& e, int m, int n, f32x4 v) {
     store4(static_cast<T*>(e.out) + (size_t)m * e.ldo + n, v[0], v[1], v[2], v[3]);
   }
@@ -54,6 +58,9 @@ struct Epi<EPI_RESID, T> {
 template <class T>
 struct Epi<EPI_GELU, T> {
   static constexpr bool kGlu = false;
+  static constexpr bool kRow = true;
+  __device__ static T* out_row(const EpiParams& e, int m) { return static_cast<T*>(e.out) + (size_t)m * e.ldo; }
+  __device__ static f32x4 row_out(f32x4 v) { return f32x4{gelu_act<T>(v[0]), gelu_act<T>(v[1]), gelu_act<T>(v[2]), gelu_act<T>(v[3])}; }
   __device__ static void apply(const EpiParams& e, int m, int n, f32x4 v) {
     store4(static_cast<T*>(e.out) + (size_t)m * e.ldo + n, gelu_act<T>(v[0]), gelu_act<T>(v[1]),
            gelu_act<T>(v[2]), gelu_act<T>(v[3]));
@@ -62,6 +69,33 @@ struct Epi<EPI_GELU, T> {
 template <class T>
 struct Epi<EPI_FUSION1, T> {
   static constexpr bool kGlu = false;
+  static constexpr bool kTile = true;  // bf16 kernels; split is a multiple of every strip's width
+  template <int TN, int TM>
+  __device__ static void tile(const EpiParams& e, const GemmProblem& p, const f32x4 (&acc)[TN][TM], int mb, int nb,
+                              int lane) {
+    const int fr = lane & 15, fq = lane >> 4;
+#pragma unroll
+    for (int a = 0; a < TN; a += 2)
+#pragma unroll
+      for (int b = 0; b < TM; ++b) {
+        const int m = mb + 16 * b + fr, n = nb + 16 * a;
+        if (nb < e.split) {
+          bf16x4 h[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const float4 c = *reinterpret_cast<const float4*>(e.bias + min(n + 16 * i, p.N - 16) + 4 * fq);
+            const f32x4 v = acc[a + i][b];
+            h[i] = bf16x4{(bf16)gelu_act<T>(v[0] + c.x), (bf16)gelu_act<T>(v[1] + c.y), (bf16)gelu_act<T>(v[2] + c.z),
+                          (bf16)gelu_act<T>(v[3] + c.w)};
+          }
+          store_rows(reinterpret_cast<bf16*>(e.out) + (size_t)m * e.ldo, n, e.split, m < p.M, h[0], h[1], fq);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            if (m < p.M && n + 16 * i + 4 * fq < p.N) apply(e, m, n + 16 * i + 4 * fq, acc[a + i][b]);
+        }
+      }
+  }
   __device__ static void apply(const EpiParams& e, int m, int n, f32x4 v) {
     const float4 b = *reinterpret_cast<const float4*>(e.bias + n);
     if (n < e.split) {
@@ -87,6 +121,9 @@ struct Epi<EPI_FUSION2, T> {
 template <class T>
 struct Epi<EPI_SILU, T> {
   static constexpr bool kGlu = false;
+  static constexpr bool kRow = true;
+  __device__ static T* out_row(const EpiParams& e, int m) { return static_cast<T*>(e.out) + (size_t)m * e.ldo; }
+  __device__ static f32x4 row_out(f32x4 v) { return f32x4{silu_act<T>(v[0]), silu_act<T>(v[1]), silu_act<T>(v[2]), silu_act<T>(v[3])}; }
   __device__ static void apply(const EpiParams& e, int m, int n, f32x4 v) {
     store4(static_cast<T*>(e.out) + (size_t)m * e.ldo + n, silu_act<T>(v[0]), silu_act<T>(v[1]),
            silu_act<T>(v[2]), silu_act<T>(v[3]));
@@ -178,18 +215,19 @@ struct Epi<EPI_QKV_ROPE, T> {
   // stores; V strips are staged feature-major and leave as 16-byte runs of 8 tokens of a
   // V^T row.  Two phases with a block barrier between them (every wave of the block runs
   // this function; the barrier orders each wave's LDS writes before its reads).
-  template <int TN, int TM>
+  // B0, NB: the row subtiles to store, [B0, B0 + NB) of the tile (mb is the first one's row).
+  template <int TN, int TM, int B0 = 0, int NB = TM>
   __device__ static void tile_lds(const EpiParams& e, const GemmProblem& p, const f32x4 (&acc)[TN][TM], int mb,
                                   int nb, int lane, char* lds) {
-    constexpr int WTN = TN * 16, WTM = TM * 16;
+    constexpr int WTN = TN * 16, WTM = NB * 16;
     const int fr = lane & 15, fq = lane >> 4;
     if (e.dh % WTN != 0) {  // the same for every wave of the grid
 #pragma unroll
       for (int a = 0; a < TN; ++a)
 #pragma unroll
-        for (int b = 0; b < TM; ++b) {
+        for (int b = 0; b < NB; ++b) {
           const int m = mb + 16 * b + fr, n = nb + 16 * a + 4 * fq;
-          if (m < p.M && n < p.N) apply(e, m, n, acc[a][b]);
+          if (m < p.M && n < p.N) apply(e, m, n, acc[a][B0 + b]);
         }
       return;
     }
@@ -200,7 +238,7 @@ struct Epi<EPI_QKV_ROPE, T> {
     // phase 1: stage
     if (live && !is_v) {
 #pragma unroll
-      for (int b = 0; b < TM; ++b) {
+      for (int b = 0; b < NB; ++b) {
         const int r = 16 * b + fr;
         const int m = min(mb + r, p.M - 1);  // rows past M are staged but never stored
         const int bb = fdiv(m, e.l_mul, e.l_shift), l = m - bb * e.L;
@@ -208,7 +246,7 @@ struct Epi<EPI_QKV_ROPE, T> {
 #pragma unroll
         for (int a = 0; a < TN; ++a) {
           const int pl = 8 * a + 2 * fq;  // local pair index of (v0, v1); (v2, v3) is pl + 1
-          const f32x4 v = acc[a][b];
+          const f32x4 v = acc[a][B0 + b];
           const float4 rr = *reinterpret_cast<const float4*>(rp + 2 * pl);  // cos, sin of pl and pl + 1
           const float a0 = v[0] * rr.x - v[1] * rr.y, b0 = v[1] * rr.x + v[0] * rr.y;
           const float a1 = v[2] * rr.z - v[3] * rr.w, b1 = v[3] * rr.z + v[2] * rr.w;
@@ -220,10 +258,10 @@ struct Epi<EPI_QKV_ROPE, T> {
 #pragma unroll
       for (int a = 0; a < TN; ++a)
 #pragma unroll
-        for (int b = 0; b < TM; ++b)
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
           for (int jj = 0; jj < 4; ++jj)
-            *reinterpret_cast<bf16*>(lds + staged<WTM>(16 * a + 4 * fq + jj, 16 * b + fr)) = (bf16)acc[a][b][jj];
+            *reinterpret_cast<bf16*>(lds + staged<WTM>(16 * a + 4 * fq + jj, 16 * b + fr)) = (bf16)acc[a][B0 + b][jj];
     }
     __syncthreads();
     // phase 2: 16-byte chunks to the attention layouts
@@ -269,6 +307,11 @@ struct Epi<EPI_QKV_ROPE, T> {
 template <class T>
 struct Epi<EPI_GLU_SILU, T> {
   static constexpr bool kGlu = true;
+  static constexpr bool kRow = true;
+  __device__ static T* out_row(const EpiParams& e, int m) { return static_cast<T*>(e.out) + (size_t)m * e.ldo; }
+  __device__ static f32x4 row_out(f32x4 g, f32x4 u) {
+    return f32x4{silu_act<T>(g[0]) * u[0], silu_act<T>(g[1]) * u[1], silu_act<T>(g[2]) * u[2], silu_act<T>(g[3]) * u[3]};
+  }
   __device__ static void glu(const EpiParams& e, int m, int f, f32x4 g, f32x4 u) {
     store4(static_cast<T*>(e.out) + (size_t)m * e.ldo + f, silu_act<T>(g[0]) * u[0],
            silu_act<T>(g[1]) * u[1], silu_act<T>(g[2]) * u[2], silu_act<T>(g[3]) * u[3]);
@@ -277,6 +320,11 @@ struct Epi<EPI_GLU_SILU, T> {
 template <class T>
 struct Epi<EPI_GLU_GELU, T> {
   static constexpr bool kGlu = true;
+  static constexpr bool kRow = true;
+  __device__ static T* out_row(const EpiParams& e, int m) { return static_cast<T*>(e.out) + (size_t)m * e.ldo; }
+  __device__ static f32x4 row_out(f32x4 g, f32x4 u) {
+    return f32x4{gelu_act<T>(g[0]) * u[0], gelu_act<T>(g[1]) * u[1], gelu_act<T>(g[2]) * u[2], gelu_act<T>(g[3]) * u[3]};
+  }
   __device__ static void glu(const EpiParams& e, int m, int f, f32x4 g, f32x4 u) {
     store4(static_cast<T*>(e.out) + (size_t)m * e.ldo + f, gelu_act<T>(g[0]) * u[0],
            gelu_act<T>(g[1]) * u[1], gelu_act<T>(g[2]) * u[2], gelu_act<T>(g[3]) * u[3]);
@@ -361,20 +409,11 @@ hipError_t dispatch(DType dt, const GemmProblem& p, const EpiParams& e, hipStrea
     return hipGetLastError();
   }
   // tile choice by how many blocks each shape yields (256 CUs): GEMMs with many rows
-  // take 256 x 256 tiles on 8 waves, mid-size ones 128 x 128 at two blocks per CU, and
+  // take 256 x 256 tiles on 8 waves (gemm_pingpong.h), mid-size ones 128 x 128 at two blocks per CU, and
   // the narrow (N = d_model) projections 64 x 64 at three blocks per CU
   const long t256 = (long)((p.M + 255) / 256) * ((p.N + 255) / 256);
   const long t128 = (long)((p.M + 127) / 128) * ((p.N + 127) / 128);
-  if ((p.M >= 4096 || p.N >= 16384) && t256 >= 128) {
-    if constexpr (K == EPI_GLU_SILU || K == EPI_GLU_GELU) {
-      // one block per CU runs in rounds of 256: 256 x 192 tiles (waves 64 x 96) win when
-      // they fill the last round better (26B-class gate/up, 1024 x 73728: 1152 tiles of
-      // 256 x 256 = 4.5 rounds -> 1536 of 256 x 192 = 6 rounds: 747 -> 669 us)
-      const long t192 = (long)((p.M + 255) / 256) * ((p.N + 191) / 192);
-      if ((t192 + 255) / 256 * 192 < (t256 + 255) / 256 * 256) return launch_bf16<256, 192, 2, 4, 2, 1, K>(p, e, s);
-    }
-    return launch_bf16<256, 256, 2, 2, 4, 1, K>(p, e, s);
-  }
+  if ((p.M >= 4096 || p.N >= 16384) && t256 >= 128 && pingpong_ok(p)) return launch_pp<K>(p, e, s);
   if (t128 >= 256) {
     // two blocks per CU run in rounds of 512; 192 x 128 tiles win when they need fewer
     // rounds for the same rows (e.g. 768 tiles of 128 x 128 = 1.5 rounds -> 512 of 192 x 128)
@@ -582,7 +621,7 @@ hipError_t gemm(DType dt, const GemmProblem& p, EpiKind kind, const EpiParams& e
       f.out = e.part;
       f.ldo = p.N;
       f.split_stride = (size_t)p.M * p.N;
-      hipError_t err = S256 > 1 ? launch_bf16<256, 256, 2, 2, 4, 1, EPI_STORE_F32>(q, f, s)
+      hipError_t err = S256 > 1 ? launch_pp<EPI_STORE_F32>(q, f, s)  // slices of >= 8 K tiles, one operand
                                 : launch_bf16<128, 128, 2, 2, 2, 2, EPI_STORE_F32>(q, f, s);
       if (err != hipSuccess) return err;
       if (e.norm_out) {  // the ordered sum and the RMSNorm of the updated rows in one pass

@@ -41,6 +41,14 @@ struct TileLdsEpi : std::false_type {};
 template <class E>
 struct TileLdsEpi<E, std::void_t<decltype(E::kTileLds)>> : std::true_type {};
 
+// An epilogue whose result is one bf16 per product (or per gate/up pair) may define kRow:
+// row_out() converts a fragment and out_row() gives the output row m; the tile then leaves
+// in 16-byte stores (store_rows).  The output's row stride is a multiple of 8.
+template <class E, class = void>
+struct RowEpi : std::false_type {};
+template <class E>
+struct RowEpi<E, std::void_t<decltype(E::kRow)>> : std::true_type {};
+
 // An epilogue that reads other tensors may define kPre (float4 loads per fragment),
 // pre() and apply_pre(): the kernel then issues those loads before the main loop,
 // where their latency hides behind the K tiles, when the tile keeps them in at most
@@ -67,8 +75,7 @@ typedef const __attribute__((address_space(1))) void* gbl_ptr;
 // band column by column, and XCD x takes the x-th eighth of that walk: the blocks it
 // holds at once cover about band x (R / band) tiles.  The grid is then padded to a
 // multiple of 8 blocks; a padded block gets tm = tiles_m and does nothing.
-__device__ __forceinline__ void tile_of(const GemmProblem& p, int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int b = blockIdx.x;
+__device__ __forceinline__ void tile_of(const GemmProblem& p, int b, int tiles_m, int tiles_n, int& tm, int& tn) {
   if (p.band > 0) {
     const int tiles = tiles_m * tiles_n, chunk = (tiles + 7) / 8, o = (b % 8) * chunk + b / 8;
     if (o >= tiles) {
@@ -115,6 +122,85 @@ __device__ __forceinline__ void mfma_first(f32x4& acc, const bf16x8& w, const bf
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(w), "v"(a));
 }
 
+// Store of two neighbouring 16-feature blocks of 16 rows: lane holds features n0 + 4 (lane
+// >> 4) + [0, 4) of both blocks (x: the first, y: the second) for its row.  Swapping the
+// odd 16-lane groups of x with the even ones of y leaves every lane 8 consecutive features,
+// lanes fr, fr + 16, fr + 32, fr + 48 covering the row's 32 features: one 16-byte store per
+// lane in 64-byte runs instead of two 8-byte stores in 32-byte runs.
+__device__ __forceinline__ void store_rows(bf16* row, int n0, int N, bool row_ok, bf16x4 x, bf16x4 y, int fq) {
+  const uint2 xu = __builtin_bit_cast(uint2, x), yu = __builtin_bit_cast(uint2, y);
+  const auto s0 = __builtin_amdgcn_permlane16_swap(xu.x, yu.x, false, false);
+  const auto s1 = __builtin_amdgcn_permlane16_swap(xu.y, yu.y, false, false);
+  const int n = n0 + 16 * (fq & 1) + 8 * (fq >> 1);
+  if (row_ok && n < N) {
+    if (n + 8 <= N)
+      *reinterpret_cast<uint4*>(row + n) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+    else  // N is a multiple of 4
+      *reinterpret_cast<uint2*>(row + n) = make_uint2(s0[0], s1[0]);
+  }
+}
+__device__ __forceinline__ bf16x4 to_bf16x4(f32x4 v) { return bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]}; }
+
+// The epilogue of a block's BM x BN tile at (m0, n0), shared by the kernels: acc is the
+// wave's part, lane holding C[n = nb + 4*(lane>>4) + j][m = mb + (lane & 15)]; PRE: the
+// epilogue's operands are in pre already; slice: the K slice whose products these are.  smem (LDS bytes) is free once every wave has
+// left the main loop.
+template <int BM, int BN, int LDS, int WGM, int WGN, EpiKind KIND, bool PRE, int TN, int TM, class P>
+__device__ __forceinline__ void finish_tile(const GemmProblem& p, EpiParams ep, const f32x4 (&acc)[TN][TM],
+                                            const P& pre, int m0, int n0, int slice, int wave, int lane, char* smem) {
+  using E = Epi<KIND, bf16>;
+  constexpr int WTM = BM / WGM, WTN = BN / WGN;
+  const int wm = wave % WGM, wn = wave / WGM, fr = lane & 15, fq = lane >> 4;
+  const int mw = m0 + wm * WTM + fr;
+  if constexpr (KIND == EPI_STORE_F32)
+    if (p.ksplit > 1) ep.out = static_cast<float*>(ep.out) + (size_t)slice * ep.split_stride;
+  if constexpr (TileLdsEpi<E>::value) {  // the wave's whole tile, staged through LDS
+    static_assert(BM * BN * 2 <= LDS, "staging area larger than the ring");
+    __syncthreads();  // every wave has finished reading the K tiles
+    E::template tile_lds<TN, TM>(ep, p, acc, m0 + wm * WTM, n0 + wn * WTN, lane, smem + wave * (WTM * WTN * 2));
+  } else if constexpr (TileEpi<E>::value) {  // the epilogue takes the wave's whole tile
+    E::template tile<TN, TM>(ep, p, acc, m0 + wm * WTM, n0 + wn * WTN, lane);
+  } else if constexpr (RowEpi<E>::value && E::kGlu && TN % 4 == 0) {
+#pragma unroll
+    for (int b = 0; b < TM; ++b)
+#pragma unroll
+      for (int a = 0; a < TN; a += 4)
+        store_rows(E::out_row(ep, mw + b * 16), (n0 + wn * WTN + a * 16) / 2, p.N / 2, mw + b * 16 < p.M,
+                   to_bf16x4(E::row_out(acc[a][b], acc[a + 1][b])), to_bf16x4(E::row_out(acc[a + 2][b], acc[a + 3][b])),
+                   fq);
+  } else if constexpr (RowEpi<E>::value && !E::kGlu) {
+#pragma unroll
+    for (int b = 0; b < TM; ++b)
+#pragma unroll
+      for (int a = 0; a < TN; a += 2)
+        store_rows(E::out_row(ep, mw + b * 16), n0 + wn * WTN + a * 16, p.N, mw + b * 16 < p.M,
+                   to_bf16x4(E::row_out(acc[a][b])), to_bf16x4(E::row_out(acc[a + 1][b])), fq);
+  } else if constexpr (E::kGlu) {
+#pragma unroll
+    for (int a = 0; a < TN; a += 2)
+#pragma unroll
+      for (int b = 0; b < TM; ++b) {
+        const int m = mw + b * 16;
+        const int ng = n0 + wn * WTN + a * 16;  // multiple of 32: gate rows of a 32-row block
+        if (m < p.M && ng < p.N) E::glu(ep, m, ng / 2 + 4 * fq, acc[a][b], acc[a + 1][b]);
+      }
+  } else {
+    const int nw = n0 + wn * WTN + 4 * fq;
+#pragma unroll
+    for (int a = 0; a < TN; ++a)
+#pragma unroll
+      for (int b = 0; b < TM; ++b) {
+        const int m = mw + b * 16, n = nw + a * 16;
+        if (m < p.M && n < p.N) {
+          if constexpr (PRE)
+            E::apply_pre(ep, m, n, acc[a][b], pre[a][b]);
+          else
+            E::apply(ep, m, n, acc[a][b]);
+        }
+      }
+  }
+}
+
 // ------------------------------------------------------------ bf16 MFMA kernel
 template <int BM, int BN, int STAGES, int WGM, int WGN, int MINB, EpiKind KIND>
 __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm_bf16_kernel(GemmProblem p, EpiParams ep) {
@@ -136,7 +222,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm_bf16_kernel(GemmPro
   const int wm = wave % WGM, wn = wave / WGM;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   int tmi, tni;
-  tile_of(p, tiles_m, tiles_n, tmi, tni);
+  tile_of(p, blockIdx.x, tiles_m, tiles_n, tmi, tni);
   if (tmi >= tiles_m) return;  // padding of a banded grid
   const int m0 = tmi * BM, n0 = tni * BN;
   if (p.M_dev) {  // rows present this call; the grid was sized for p.M
@@ -289,40 +375,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm_bf16_kernel(GemmPro
 #pragma unroll
     for (int b = 0; b < TM; ++b) asm volatile("" : "+a"(acc[a][b]));
 
-  // lane holds C[n = nb + 4*(lane>>4) + j][m = mb + (lane & 15)]
-  const int mw = m0 + wm * WTM + fr;
-  if constexpr (KIND == EPI_STORE_F32)
-    if (p.ksplit > 1) ep.out = static_cast<float*>(ep.out) + (size_t)blockIdx.y * ep.split_stride;
-  if constexpr (TileLdsEpi<E>::value) {  // the wave's whole tile, staged through LDS
-    static_assert(BM * BN * 2 <= STAGES * STAGE_BYTES, "staging area larger than the ring");
-    __syncthreads();  // every wave has finished reading the K tiles
-    E::template tile_lds<TN, TM>(ep, p, acc, m0 + wm * WTM, n0 + wn * WTN, lane, smem + wave * (WTM * WTN * 2));
-  } else if constexpr (TileEpi<E>::value) {  // the epilogue takes the wave's whole tile
+  if constexpr (TileEpi<E>::value)  // called from here: one inlining level keeps acc in registers
     E::template tile<TN, TM>(ep, p, acc, m0 + wm * WTM, n0 + wn * WTN, lane);
-  } else if constexpr (E::kGlu) {
-#pragma unroll
-    for (int a = 0; a < TN; a += 2)
-#pragma unroll
-      for (int b = 0; b < TM; ++b) {
-        const int m = mw + b * 16;
-        const int ng = n0 + wn * WTN + a * 16;  // multiple of 32: gate rows of a 32-row block
-        if (m < p.M && ng < p.N) E::glu(ep, m, ng / 2 + 4 * fq, acc[a][b], acc[a + 1][b]);
-      }
-  } else {
-    const int nw = n0 + wn * WTN + 4 * fq;
-#pragma unroll
-    for (int a = 0; a < TN; ++a)
-#pragma unroll
-      for (int b = 0; b < TM; ++b) {
-        const int m = mw + b * 16, n = nw + a * 16;
-        if (m < p.M && n < p.N) {
-          if constexpr (PRE)
-            E::apply_pre(ep, m, n, acc[a][b], pre[a][b]);
-          else
-            E::apply(ep, m, n, acc[a][b]);
-        }
-      }
-  }
+  else
+    finish_tile<BM, BN, STAGES * STAGE_BYTES, WGM, WGN, KIND, PRE>(p, ep, acc, pre, m0, n0, blockIdx.y, wave, lane, smem);
 }
 
 // Per-XCD region rm x rn with (tiles_m / rm) * (tiles_n / rn) = 8 that minimises the
