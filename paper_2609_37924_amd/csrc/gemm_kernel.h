@@ -75,10 +75,14 @@ typedef const __attribute__((address_space(1))) void* gbl_ptr;
 // band column by column, and XCD x takes the x-th eighth of that walk: the blocks it
 // holds at once cover about band x (R / band) tiles.  The grid is then padded to a
 // multiple of 8 blocks; a padded block gets tm = tiles_m and does nothing.
+// A product whose row count is only known on the device (M_dev) is always walked in bands,
+// over the tiles of the rows present: a walk over the launch's row bound would give the
+// tiles without rows to some XCDs and leave the others all the work (1B-class head, 16 384 of
+// 32 768 rows present, 50 304 x 2 048: half of the chip idle).
 __device__ __forceinline__ void tile_of(const GemmProblem& p, int b, int tiles_m, int tiles_n, int& tm, int& tn) {
   if (p.band > 0) {
     const int tiles = tiles_m * tiles_n, chunk = (tiles + 7) / 8, o = (b % 8) * chunk + b / 8;
-    if (o >= tiles) {
+    if (b / 8 >= chunk || o >= tiles) {
       tm = tiles_m;
       tn = 0;
       return;
@@ -220,15 +224,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm_bf16_kernel(GemmPro
   // then formed in scalar registers
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WGM, wn = wave / WGM;
+  if (p.M_dev) p.M = min(*p.M_dev, p.M);  // rows present this call; the grid was sized for p.M
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   int tmi, tni;
   tile_of(p, blockIdx.x, tiles_m, tiles_n, tmi, tni);
-  if (tmi >= tiles_m) return;  // padding of a banded grid
+  if (tmi >= tiles_m) return;  // padding of a banded grid, or no rows for this block
   const int m0 = tmi * BM, n0 = tni * BN;
-  if (p.M_dev) {  // rows present this call; the grid was sized for p.M
-    p.M = min(*p.M_dev, p.M);
-    if (m0 >= p.M) return;
-  }
 
   const bf16* A1 = static_cast<const bf16*>(p.A1);
   const bf16* A2 = static_cast<const bf16*>(p.A2);
@@ -443,7 +444,7 @@ template <int BM, int BN, int ST, int WGM, int WGN, int MINB, EpiKind K>
 hipError_t launch_bf16(const GemmProblem& p0, const EpiParams& e, hipStream_t s) {
   GemmProblem p = p0;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  xcd_regions(tiles_m, tiles_n, BM, BN, p.rm, p.rn);
+  if (!p.M_dev) xcd_regions(tiles_m, tiles_n, BM, BN, p.rm, p.rn);
   // one block per CU for the 8-wave tiles, MINB per CU otherwise (LDS bounds both)
   if (MINB <= 2) xcd_patch(p.rm, p.rn, BM, BN, 32 * MINB, p.gm, p.gn);
   p.band = p.rm > 0 ? 0 : xcd_band(tiles_m, BM, BN, 32 * MINB);

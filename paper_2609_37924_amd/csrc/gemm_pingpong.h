@@ -105,8 +105,8 @@ __global__ __launch_bounds__(512, 1) void gemm_pp_kernel(GemmProblem p, EpiParam
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WGM, wn = wave / WGM;
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   if (p.M_dev) p.M = min(*p.M_dev, p.M);  // rows present this call; the grid was sized for p.M
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
 
   // the tile at position t of this launch's walk (K slices one after the other): its
   // corner and its K tiles [kt_base, kt_base + nk)
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(512, 1) void gemm_pp_kernel(GemmProblem p, EpiParam
       int tm, tn;
       const int s = t / grid_tiles;
       tile_of(p, t - s * grid_tiles, tiles_m, tiles_n, tm, tn);
-      if (tm >= tiles_m || tm * BM >= p.M) continue;  // padding of a banded grid; absent rows
+      if (tm >= tiles_m) continue;  // padding of a banded grid, or no rows here
       o.m0 = __builtin_amdgcn_readfirstlane(tm * BM);
       o.n0 = __builtin_amdgcn_readfirstlane(tn * BN);
       o.slice = s;
@@ -303,7 +303,7 @@ template <EpiKind K>
 hipError_t launch_pp(const GemmProblem& p0, const EpiParams& e, hipStream_t s) {
   GemmProblem p = p0;
   const int tiles_m = (p.M + 255) / 256, tiles_n = (p.N + 255) / 256;
-  xcd_regions(tiles_m, tiles_n, 256, 256, p.rm, p.rn);
+  if (!p.M_dev) xcd_regions(tiles_m, tiles_n, 256, 256, p.rm, p.rn);
   xcd_patch(p.rm, p.rn, 256, 256, 32, p.gm, p.gn);
   p.band = p.rm > 0 ? 0 : xcd_band(tiles_m, 256, 256, 32);
   // a multiple of 8 either way, so that position b + kPpBlocks stays on b's XCD

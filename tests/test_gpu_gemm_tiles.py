@@ -1,0 +1,81 @@
+"""The large-tile matrix products at the edges of their tiles and K tiles.
+
+The vocabulary head of a model without layers is one product of known operands: its
+normalised input is read back (bf16, exact as float32) and the logits are compared with the
+float64 product of that input and the stored weights.  d_model 128, 192 and 320 give two,
+three and five K tiles; the row counts and vocabularies leave partial 256-row and 256-column
+tiles and grids with and without an even split over the chip's eight dies.
+"""
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _model(d, vocab, B, P, G):
+    import paper_2609_37924_amd as tadm
+    cfg = synth.get_config("small", d_model=d, n_heads=d // 64, n_kv_heads=d // 64, d_ffn=64, vocab=vocab,
+                           n_anchor=0, n_denoise=0)
+    dev = torch.device("cuda:0")
+    tensors = [t.to(dev) for t in synth.make_weights(cfg, perturb=True)]
+    m = tadm.load_model(cfg, tensors, max_batch=B, max_seq=P + G, stream=torch.cuda.current_stream().cuda_stream)
+    return tadm, cfg, dev, tensors, m
+
+
+@pytest.mark.parametrize("d,vocab,B,G", [(128, 32768, 1, 257), (192, 33028, 1, 300), (320, 33028, 3, 100),
+                                         (128, 16640, 2, 512), (192, 65540, 1, 63)])
+def test_large_tile_product(d, vocab, B, G):
+    tadm, cfg, dev, tensors, m = _model(d, vocab, B, 1, G)
+    try:
+        L = G + 1
+        z = torch.randint(0, vocab, (B, L), dtype=torch.int32).to(dev)
+        cache = tadm.tadm_cache_create(m, B, L)
+        tadm.tadm_anchor_forward(m, None, z, B, L, 1, 1, cache)
+        logits = torch.full((B, G, vocab), float("nan"), device=dev)
+        nxt = torch.empty_like(z)
+        tadm.tadm_denoise_step(m, None, z, B, L, 1, cache, tadm.step_args(1, 1, 0, 0, 3, 1.0), logits, nxt)
+        x = torch.empty(B, G, d, device=dev)
+        tadm.tadm_debug_read(m, tadm.TAP_FINAL, x)
+        torch.cuda.synchronize()
+        w = tensors[2].double()
+        ref = x.double().reshape(-1, d) @ w.T
+        # float32 accumulation of d exact products: at most d roundings of 2^-24 of the sum of magnitudes
+        bound = d * 2.0 ** -24 * (x.double().abs().reshape(-1, d) @ w.abs().T)
+        assert ((logits.double().reshape(-1, vocab) - ref).abs() <= bound).all()
+        tadm.tadm_cache_destroy(cache)
+    finally:
+        tadm.tadm_model_destroy(m)
+
+
+@pytest.mark.parametrize("vocab,B,G,masked", [(32768, 4, 256, 3), (40960, 4, 256, 129), (40964, 5, 250, 250),
+                                              (65536, 2, 700, 0)])
+def test_masked_only_head_with_few_rows(vocab, B, G, masked):
+    """The masked-only head, whose row count is known on the device alone, against the sampler
+    on the logits of every row: the same tokens and confidences at any share of masked rows
+    (the first `masked` positions of each row; a row bound of all positions)."""
+    tadm, cfg, dev, tensors, m = _model(192, vocab, B, 1, G)
+    try:
+        L = G + 1
+        z = torch.randint(0, vocab, (B, L), dtype=torch.int32)
+        z[:, 1:1 + masked] = vocab
+        z = z.to(dev)
+        cache = tadm.tadm_cache_create(m, B, L)
+        tadm.tadm_anchor_forward(m, None, z, B, L, 1, 1, cache)
+        args = tadm.step_args(1, 1, masked, 5, 77, 1.0)
+        out = []
+        for logits in (torch.empty(B, G, vocab, device=dev), None):
+            nxt = torch.empty_like(z)
+            ch = torch.empty(B, G, dtype=torch.int32, device=dev)
+            cf = torch.empty(B, G, device=dev)
+            tadm.tadm_denoise_step(m, None, z, B, L, 1, cache, args, logits, nxt)
+            tadm.tadm_debug_read(m, tadm.TAP_CHOICE, ch)
+            tadm.tadm_debug_read(m, tadm.TAP_CONF, cf)
+            torch.cuda.synchronize()
+            out.append((nxt, ch, cf))
+        for a, b in zip(*out):
+            assert torch.equal(a, b)
+        tadm.tadm_cache_destroy(cache)
+    finally:
+        tadm.tadm_model_destroy(m)
