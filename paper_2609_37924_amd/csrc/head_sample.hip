@@ -40,17 +40,19 @@ struct Epi<EPI_SAMPLE, T> {
     static_assert(TN * 16 == SAMPLE_GROUP, "one wave column strip must be one normaliser group");
     const int fr = lane & 15, fq = lane >> 4;
     const int g = nb / SAMPLE_GROUP;
+    f32x4 rot[TN][TM];  // row subtile b in rot[.][0]: the others move down one place per pass
+#pragma unroll
+    for (int a = 0; a < TN; ++a)
+#pragma unroll
+      for (int k = 0; k < TM; ++k) rot[a][k] = acc[a][k];
 #pragma unroll 1
     for (int b = 0; b < TM; ++b) {
-      // this row subtile's accumulators, picked with static indices (a runtime index
-      // into acc would move the whole tile to scratch)
       f32x4 cb[TN];
 #pragma unroll
       for (int a = 0; a < TN; ++a) {
-        cb[a] = acc[a][0];
+        cb[a] = rot[a][0];
 #pragma unroll
-        for (int k = 1; k < TM; ++k)
-          if (b == k) cb[a] = acc[a][k];
+        for (int k = 1; k < TM; ++k) rot[a][k - 1] = rot[a][k];
       }
       const int m = mb + 16 * b + fr;
       const bool row_ok = m < p.M;

@@ -71,10 +71,15 @@ __device__ __forceinline__ float own_log(float x) {
 // e^r = 1 + r + r^2 c(r) with c the Taylor series to r^5/7!, r = y - k ln 2 (Cody-Waite:
 // rh = y - k ln2_hi exact, r = rh - k ln2_lo), summed as 1 + (rh + (r^2 c - k ln2_lo)) so
 // that the rounding of r does not enter the linear term (within 1 ulp for y in [-30, 0]).
+// k is rounded to an integer by adding 1.5 2^23 (|k| < 2^22), which also leaves k in the low
+// bits of the sum, where one shift-and-add turns it into the exponent field of 2^(k + bias);
+// k ln2_hi has at most 21 significant bits, so y - k ln2_hi is one fused operation with the
+// bits of the separately rounded ones.
 __device__ __forceinline__ float own_exp_core(float y, int bias) {
   const float LN2_HI = bits_f(0x3F317200u), LN2_LO = bits_f(0x35BFBE8Eu);
-  const float k = rintf(y * bits_f(0x3FB8AA3Bu));
-  const float rh = y - k * LN2_HI;
+  const float t = y * bits_f(0x3FB8AA3Bu) + 12582912.0f;
+  const float k = t - 12582912.0f;
+  const float rh = __builtin_fmaf(k, -LN2_HI, y);
   const float kl = k * LN2_LO;
   const float r = rh - kl;
   float c = bits_f(0x39500D01u);       // 1/5040
@@ -85,7 +90,7 @@ __device__ __forceinline__ float own_exp_core(float y, int bias) {
   c = c * r + 0.5f;
   const float q = (r * r) * c;
   const float p = 1.0f + (rh + (q - kl));
-  const float scale = __uint_as_float((uint32_t)((int)k + 127 + bias) << 23);
+  const float scale = __uint_as_float((__float_as_uint(t) << 23) + ((uint32_t)(127 + bias) << 23));
   return p * scale;
 }
 
