@@ -4,8 +4,11 @@
 // below; the tile shape is picked per call from the number of blocks it yields.
 // float32 operands (small fp32 models) run on a register-blocked VALU kernel with
 // the same epilogues.
+#include <algorithm>
+
 #include "gemm_kernel.h"
 #include "gemm_pingpong.h"
+#include "gemm_ring.h"
 
 namespace tadm {
 namespace {
@@ -401,6 +404,20 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmProblem p, EpiParams 
   }
 }
 
+// Grids that leave CUs short of blocks: 64 x 64 tiles on the deep ring, three blocks per CU;
+// with at most 64 such tiles 32 x 32 ones, four times the blocks (64 x 3 072 x 2 048: 12.2 ->
+// 9.1 us; 64 x 16 384 x 2 048 has 256 tiles: 18.4 against 25.6).  Epilogues that pair weight
+// blocks keep 64 columns.
+template <EpiKind K>
+hipError_t launch_small(const GemmProblem& p, const EpiParams& e, hipStream_t s) {
+  using E = Epi<K, bf16>;
+  if constexpr (!E::kGlu && !TileEpi<E>::value && !RowEpi<E>::value) {
+    const long t64 = (long)((p.M + 63) / 64) * ((p.N + 63) / 64);
+    if (t64 * p.ksplit <= 64) return launch_ring<32, 32, 8, 2, K>(p, e, s);
+  }
+  return launch_ring<64, 64, 3, 3, K>(p, e, s);
+}
+
 template <EpiKind K>
 hipError_t dispatch(DType dt, const GemmProblem& p, const EpiParams& e, hipStream_t s) {
   if (dt == F32) {
@@ -422,7 +439,7 @@ hipError_t dispatch(DType dt, const GemmProblem& p, const EpiParams& e, hipStrea
     if (cost192 < cost128) return launch_bf16<192, 128, 2, 2, 2, 2, K>(p, e, s);
     return launch_bf16<128, 128, 2, 2, 2, 2, K>(p, e, s);
   }
-  return launch_bf16<64, 64, 2, 2, 2, 3, K>(p, e, s);
+  return launch_small<K>(p, e, s);
 }
 
 // out[m, n] = row1[m] * sum_s part[s, m, n], s ascending (float4 granules, N % 4 == 0)
@@ -517,6 +534,7 @@ __global__ __launch_bounds__(256) void resid_reduce_rms_kernel(const float* part
     const int c = (t + 256 * i) * 4;
     if (c < N) {
       float4 acc = *reinterpret_cast<const float4*>(part + (size_t)m * N + c);
+#pragma unroll 4
       for (int k = 1; k < S; ++k) {
         const float4 v = *reinterpret_cast<const float4*>(part + k * MN + (size_t)m * N + c);
         acc.x += v.x;
@@ -596,12 +614,44 @@ int resid_slices(int M, int N, int K) {
   return best;
 }
 
+// K slices of a residual product of few tiles, on the 64 x 64 ring: enough slices for 256 to
+// 320 blocks, each of at least three K tiles (384 x 768 x 2 048, 72 tiles, four slices: 16.5 ->
+// 6.8 us; 64 x 2 048 x 8 192, 32 tiles, eight slices: 25 us on 256 x 256 slices -> 11.0); the
+// slice sum takes the place of the RMSNorm that follows.  From 160 tiles on the unsplit ring
+// is as fast (192 tiles, K = 512: 5.6 against 6.3 us).
+int resid_slices64(int M, int N, int K) {
+  const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64);
+  const int nk = K / 64;
+  if (N % 4 || tiles > 160) return 1;
+  const int S = (int)std::min<long>(std::min<long>(nk / 3, (long)(GEMM_SMALL_PART / 4096) / tiles), 16);
+  return S < 2 ? 1 : S;
+}
+
+// The K slices of a residual product and the tiles they run on.
+enum SliceTiles { SLICE_NONE, SLICE_64, SLICE_128, SLICE_256 };
+SliceTiles resid_plan(int M, int N, int K, int* S) {
+  if ((*S = resid_slices64(M, N, K)) > 1) return SLICE_64;
+  if ((*S = resid_slices256(M, N, K)) > 1) return SLICE_256;
+  if ((*S = resid_slices(M, N, K)) > 1) return SLICE_128;
+  return SLICE_NONE;
+}
+
+// The slices' products of q (ksplit set) to f.out [S, M, N].
+hipError_t launch_slices(SliceTiles t, const GemmProblem& q, const EpiParams& f, hipStream_t s) {
+  switch (t) {
+    case SLICE_64: return launch_ring<64, 64, 4, 2, EPI_STORE_F32>(q, f, s);
+    case SLICE_256: return launch_pp<EPI_STORE_F32>(q, f, s);  // slices of >= 8 K tiles, one operand
+    default: return launch_bf16<128, 128, 2, 2, 2, 2, EPI_STORE_F32>(q, f, s);
+  }
+}
+
 }  // namespace
 
 int gemm_split_slices(int M, int N, int K) { return split_slices(M, N, K); }
 int gemm_resid_slices(int M, int N, int K) {
-  const int S256 = resid_slices256(M, N, K);
-  return S256 > 1 ? S256 : resid_slices(M, N, K);
+  int S;
+  resid_plan(M, N, K, &S);
+  return S;
 }
 bool gemm_resid_norms(int M, int N, int K) { return gemm_resid_slices(M, N, K) > 1 && N % 4 == 0 && N <= 8192; }
 
@@ -612,8 +662,8 @@ hipError_t gemm(DType dt, const GemmProblem& p, EpiKind kind, const EpiParams& e
     if (splitk_scale(p, e, s, &err)) return err;
   }
   if (kind == EPI_RESID && dt == BF16 && e.part && !p.M_dev && p.K1 == p.K) {
-    const int S256 = resid_slices256(p.M, p.N, p.K);
-    const int S = S256 > 1 ? S256 : resid_slices(p.M, p.N, p.K);
+    int S;
+    const SliceTiles tiles = resid_plan(p.M, p.N, p.K, &S);
     if (S > 1) {  // the slices' products to part [S, M, N], then an ordered sum into resid
       GemmProblem q = p;
       q.ksplit = S;
@@ -621,8 +671,7 @@ hipError_t gemm(DType dt, const GemmProblem& p, EpiKind kind, const EpiParams& e
       f.out = e.part;
       f.ldo = p.N;
       f.split_stride = (size_t)p.M * p.N;
-      hipError_t err = S256 > 1 ? launch_pp<EPI_STORE_F32>(q, f, s)  // slices of >= 8 K tiles, one operand
-                                : launch_bf16<128, 128, 2, 2, 2, 2, EPI_STORE_F32>(q, f, s);
+      hipError_t err = launch_slices(tiles, q, f, s);
       if (err != hipSuccess) return err;
       if (e.norm_out) {  // the ordered sum and the RMSNorm of the updated rows in one pass
         if (!gemm_resid_norms(p.M, p.N, p.K) || !e.norm_g) return hipErrorInvalidValue;

@@ -172,7 +172,7 @@ __device__ __forceinline__ void finish_tile(const GemmProblem& p, EpiParams ep, 
         store_rows(E::out_row(ep, mw + b * 16), (n0 + wn * WTN + a * 16) / 2, p.N / 2, mw + b * 16 < p.M,
                    to_bf16x4(E::row_out(acc[a][b], acc[a + 1][b])), to_bf16x4(E::row_out(acc[a + 2][b], acc[a + 3][b])),
                    fq);
-  } else if constexpr (RowEpi<E>::value && !E::kGlu) {
+  } else if constexpr (RowEpi<E>::value && !E::kGlu && TN % 2 == 0) {
 #pragma unroll
     for (int b = 0; b < TM; ++b)
 #pragma unroll

@@ -131,6 +131,9 @@ int gemm_split_slices(int M, int N, int K);
 // K slices of a bf16 EPI_RESID product given a part buffer (1: no split; else
 // part holds slices * M * N floats): long K with few 128 x 128 tiles.
 int gemm_resid_slices(int M, int N, int K);
+// Floats that the part buffer of a product sliced on 64 x 64 tiles never exceeds (at most 320
+// blocks): a part buffer of that size from the start grows only for larger products.
+constexpr size_t GEMM_SMALL_PART = 320 * 64 * 64;
 // Whether a bf16 EPI_RESID product of this shape (split over K) can also write the RMSNorm
 // of its updated rows (EpiParams::norm_out); otherwise the caller normalises them.
 bool gemm_resid_norms(int M, int N, int K);

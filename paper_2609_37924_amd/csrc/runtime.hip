@@ -400,6 +400,17 @@ static tadm_status ws_alloc(tadm_model* m, void** p, size_t bytes) {
   return TADM_OK;
 }
 
+// Workspace of K-slice products (grown on demand).
+static tadm_status ensure_kpart(tadm_model* m, size_t floats) {
+  Workspace& s = m->ws;
+  if (s.kpart_cap >= floats) return TADM_OK;
+  if (s.kpart) HIPCHK(hipFree(s.kpart));
+  s.kpart = nullptr;
+  HIPCHK(hipMalloc((void**)&s.kpart, floats * 4));
+  s.kpart_cap = floats;
+  return TADM_OK;
+}
+
 static tadm_status ensure_workspace(tadm_model* m) {
   Workspace& w = m->ws;
   if (w.n_tok) return TADM_OK;
@@ -442,6 +453,7 @@ static tadm_status ensure_workspace(tadm_model* m) {
   TRY(ws_alloc(m, (void**)&w.xhat, N * 4));
   TRY(ws_alloc(m, (void**)&w.hq, N * 8));
   TRY(ws_alloc(m, (void**)&w.rscale, N * 4));
+  if (m->dt == BF16) TRY(ensure_kpart(m, GEMM_SMALL_PART));
   w.n_tok = (int)N;
   w.n_canvas = (int)N;
   return TADM_OK;
@@ -454,17 +466,6 @@ static tadm_status ensure_logits(tadm_model* m, size_t n) {
   w.logits = nullptr;
   HIPCHK(hipMalloc((void**)&w.logits, n * 4));
   w.logits_cap = n;
-  return TADM_OK;
-}
-
-// Workspace of K-slice products (grown on demand).
-static tadm_status ensure_kpart(tadm_model* m, size_t floats) {
-  Workspace& s = m->ws;
-  if (s.kpart_cap >= floats) return TADM_OK;
-  if (s.kpart) HIPCHK(hipFree(s.kpart));
-  s.kpart = nullptr;
-  HIPCHK(hipMalloc((void**)&s.kpart, floats * 4));
-  s.kpart_cap = floats;
   return TADM_OK;
 }
 

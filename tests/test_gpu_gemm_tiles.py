@@ -1,10 +1,10 @@
-"""The large-tile matrix products at the edges of their tiles and K tiles.
+"""The matrix products at the edges of their tiles and K tiles.
 
 The vocabulary head of a model without layers is one product of known operands: its
 normalised input is read back (bf16, exact as float32) and the logits are compared with the
-float64 product of that input and the stored weights.  d_model 128, 192 and 320 give two,
-three and five K tiles; the row counts and vocabularies leave partial 256-row and 256-column
-tiles and grids with and without an even split over the chip's eight dies.
+float64 product of that input and the stored weights.  d_model 64 to 704 gives one
+to eleven K tiles; the row counts and vocabularies leave partial 256, 64 and 32-row tiles and
+grids with and without an even split over the chip's eight dies.
 """
 import pytest
 import torch
@@ -25,8 +25,10 @@ def _model(d, vocab, B, P, G):
 
 
 @pytest.mark.parametrize("d,vocab,B,G", [(128, 32768, 1, 257), (192, 33028, 1, 300), (320, 33028, 3, 100),
-                                         (128, 16640, 2, 512), (192, 65540, 1, 63)])
-def test_large_tile_product(d, vocab, B, G):
+                                         (128, 16640, 2, 512), (192, 65540, 1, 63),
+                                         (64, 300, 1, 63), (64, 516, 1, 1), (128, 1028, 1, 65), (320, 5000, 1, 129),
+                                         (704, 96, 2, 33), (640, 3000, 3, 100)])
+def test_product_tiles(d, vocab, B, G):
     tadm, cfg, dev, tensors, m = _model(d, vocab, B, 1, G)
     try:
         L = G + 1
@@ -76,6 +78,39 @@ def test_masked_only_head_with_few_rows(vocab, B, G, masked):
             out.append((nxt, ch, cf))
         for a, b in zip(*out):
             assert torch.equal(a, b)
+        tadm.tadm_cache_destroy(cache)
+    finally:
+        tadm.tadm_model_destroy(m)
+
+
+@pytest.mark.parametrize("d,F,B,L", [(128, 192, 1, 1), (128, 1024, 1, 64), (256, 512, 1, 65), (768, 2048, 1, 385),
+                                     (768, 2048, 2, 640)])
+def test_residual_products_in_slices(d, F, B, L):
+    """A layer whose residual products are split over K (one to sixteen slices, the slice sum
+    writing the following norm) against the float64 layer of the oracle, at the bf16 bar."""
+    import numpy as np
+
+    import paper_2609_37924_amd as tadm
+    from oracle import network as N
+
+    cfg = synth.get_config("small", d_model=d, n_heads=d // 64, n_kv_heads=d // 64, d_ffn=F, vocab=256, n_anchor=2,
+                           n_denoise=0)
+    dev = torch.device("cuda:0")
+    tensors = synth.make_weights(cfg, perturb=True)
+    m = tadm.load_model(cfg, [t.to(dev) for t in tensors], max_batch=B, max_seq=L,
+                        stream=torch.cuda.current_stream().cuda_stream)
+    try:
+        z = torch.randint(0, cfg["vocab"], (B, L), generator=torch.Generator().manual_seed(3), dtype=torch.int32)
+        cache = tadm.tadm_cache_create(m, B, L)
+        tadm.tadm_anchor_forward(m, None, z.to(dev), B, L, 1, 1, cache)
+        h = torch.empty(B, L, d, device=dev)
+        tadm.tadm_cache_read(cache, tadm.CACHE_H, h)
+        torch.cuda.synchronize()
+        net = N.Network(N.Weights(cfg, [s[0] for s in synth.weight_specs(cfg)], tensors))
+        pos = np.arange(L)
+        for b in range(B):
+            ref = net.anchor_cache(net.shared(z[b].numpy(), pos), pos)["h"]
+            assert np.allclose(h[b].cpu().numpy(), ref, rtol=2e-2, atol=2e-2)
         tadm.tadm_cache_destroy(cache)
     finally:
         tadm.tadm_model_destroy(m)
