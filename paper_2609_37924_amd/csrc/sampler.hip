@@ -213,19 +213,23 @@ __global__ __launch_bounds__(256) void sample_kernel(const float* logits, const 
 
 // grid (Lc, B), NUC_THREADS threads: the nucleus threshold of each masked position.
 // Weights q_v = rint(exp(l'_v - m) 2^40) (int64), Q = sum q_v, target = ceil(top_p Q) (exact,
-// in 128-bit integers); tau is found by four radix passes over the 41-bit weights (digits of
-// 11, 11, 11 and 8 bits, high to low): each pass sums, per digit, the weights of the entries
-// that share the digits chosen so far, and keeps the highest digit at which the weights
-// above plus that digit's reach the target.  All sums are integers: any order, same tau.
-// The first pass also accumulates Q.  Digit 0 collects every small weight of a pass (most
-// of the vocabulary), so it is not accumulated by atomics: its sum is the pass's total (Q,
-// then the previous pass's chosen digit's sum) minus the other digits'.
-// A weight is held as the float w = rint(exp(l'_v - m) 2^40), an integer below 2^41 with
-// 24 significant bits, so its digits and prefixes are exact float operations:
-// floor(w 2^-s) is q >> s, and floor(w 2^-s) - floor(w 2^-(s+b)) 2^b is its b-bit digit.
+// in 128-bit integers); tau = the largest weight whose tail sum reaches the target, found by
+// radix selection.  A weight is held as the float w = q (an integer below 2^41 with 24
+// significant bits, so exact), and positive floats order as their bits do: the digits are
+// fields of w's bits, which spread the weights evenly over the bins whatever their range
+// (32 bins an octave), so one pass over the row leaves the boundary bin a small share of it
+// (a digit of q itself leaves most of a flat row's weights in its lowest bin).  The second
+// pass gathers that bin's weights in LDS, and the other two digits (11 and 7 bits) are
+// found on the list; a bin with more than NUC_LIST weights is walked in the row instead.  Each
+// digit sums, per bin, the weights that share the digits chosen so far, and keeps the highest
+// bin at which the weights above plus the bin's reach the target.  All sums are integers:
+// any order, same tau.
+// Bound by reading the row from memory (three times; rows in flight outgrow the L2) and the
+// exponentials: 768 rows of 128 256, top_p 0.9: four passes over the row, one exponential per
+// entry each, 1 048 us; now 259 us.
 // PER > 0: V <= NUC_THREADS * PER and V % 4 == 0; each thread keeps the weights of its PER
-// entries in registers, read once as float4.  PER = 0: every pass recomputes them.
-constexpr int NUC_THREADS = 1024;
+// entries in registers, read once as float4.  PER = 0: every pass reads the row.
+constexpr int NUC_THREADS = 1024, NUC_LIST = 4096;
 template <int PER>
 __global__ __launch_bounds__(NUC_THREADS) void nucleus_kernel(const float* logits, const int32_t* row_map,
                                                               const int32_t* canvas, int L, int off, int Lc, int V,
@@ -235,16 +239,45 @@ __global__ __launch_bounds__(NUC_THREADS) void nucleus_kernel(const float* logit
   constexpr bool CACHED = PER > 0;
   constexpr int NE = CACHED ? PER : 1;
   constexpr float TWO40 = 1099511627776.0f;
-  __shared__ unsigned long long hist[2048];
+  constexpr uint32_t ONE = 0x3F800000u;  // bits of the smallest positive weight
+  constexpr int BINS = 2048;             // first digit: (bits - ONE) >> 18, at most 41 * 32
+  __shared__ unsigned long long hist[BINS];
+  __shared__ uint32_t list[NUC_LIST];
   __shared__ float s_f[NW];
   __shared__ unsigned long long s_u[NW];
   __shared__ unsigned long long s_sel[3];
+  __shared__ float s_y[2];
+  __shared__ int s_n;
   const int j = blockIdx.x, b = blockIdx.y, row = b * Lc + j;
   if (canvas[(size_t)b * L + off + j] != mask_id || (row_map && row_map[row] < 0)) return;
   const float* lg = logits + (size_t)(row_map ? row_map[row] : row) * V;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // cached entry i of this thread: v = 4 (tid + NUC_THREADS (i / 4)) + i % 4
   auto vof = [&](int i) { return 4 * (tid + NUC_THREADS * (i >> 2)) + (i & 3); };
+  // f(l'_v) for every entry of the row, four float4 loads in flight per thread
+  auto for_each_logit = [&](auto f) {
+    if ((V & 3) == 0) {
+      const int nq = V / 4;
+      for (int q0 = tid; q0 < nq; q0 += 4 * NUC_THREADS) {
+        float4 x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int q = q0 + u * NUC_THREADS;
+          x[u] = q < nq ? *reinterpret_cast<const float4*>(lg + 4 * q)
+                        : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          f(x[u].x * inv_temp);
+          f(x[u].y * inv_temp);
+          f(x[u].z * inv_temp);
+          f(x[u].w * inv_temp);
+        }
+      }
+    } else {
+      for (int v = tid; v < V; v += NUC_THREADS) f(lg[v] * inv_temp);
+    }
+  };
 
   float ev[NE];  // l'_v, then the weight w_v
   float mx = -INFINITY;
@@ -260,11 +293,16 @@ __global__ __launch_bounds__(NUC_THREADS) void nucleus_kernel(const float* logit
       mx = fmaxf(mx, fmaxf(fmaxf(ev[i], ev[i + 1]), fmaxf(ev[i + 2], ev[i + 3])));
     }
   } else {
-    for (int v = tid; v < V; v += NUC_THREADS) mx = fmaxf(mx, lg[v] * inv_temp);
+    for_each_logit([&](float l) { mx = fmaxf(mx, l); });
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
   if (lane == 0) s_f[wave] = mx;
+  for (int i = tid; i < BINS; i += NUC_THREADS) hist[i] = 0;
+  if (tid == 0) {
+    s_n = 0;
+    s_sel[0] = s_sel[1] = 0;  // stays so only for a row without a finite weight
+  }
   __syncthreads();
   mx = s_f[0];
   for (int w = 1; w < NW; ++w) mx = fmaxf(mx, s_f[w]);
@@ -276,8 +314,8 @@ __global__ __launch_bounds__(NUC_THREADS) void nucleus_kernel(const float* logit
       asm volatile("" : "+v"(ev[i]), "+v"(ev[i + 1]), "+v"(ev[i + 2]), "+v"(ev[i + 3])::"memory");
     }
   }
-  // calls f(w) for every entry of the row (the cached padding entries have w = 0)
-  auto for_each_weight = [&](auto f) {
+  // calls f(w) for the row's weights; PER = 0: for those with y_lo <= l' - m <= y_hi only
+  auto for_each_weight = [&](float y_lo, float y_hi, auto f) {
     if constexpr (CACHED) {
 #pragma unroll
       for (int i = 0; i < NE; i += 4) {
@@ -291,19 +329,48 @@ __global__ __launch_bounds__(NUC_THREADS) void nucleus_kernel(const float* logit
         f(w3);
       }
     } else {
-      for (int v = tid; v < V; v += NUC_THREADS) f(rintf(own_exp(lg[v] * inv_temp - mx) * TWO40));
+      for_each_logit([&](float l) {
+        const float y = l - mx;
+        if (y >= y_lo && y <= y_hi) f(rintf(own_exp_sel(y) * TWO40));
+      });
+    }
+  };
+  // wave 0: the boundary among nb bins of hist (lane l owns bins [l c, (l + 1) c); suffix
+  // sums over lanes, high to low): its number, the weight above it and its own weight
+  auto select = [&](int nb, unsigned long long above, unsigned long long target) {
+    if (wave == 0) {
+      const int c = nb / 64;
+      unsigned long long own = 0;
+      for (int i = 0; i < c; ++i) own += hist[lane * c + i];
+      unsigned long long suf = own;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long t = __shfl_down(suf, o, 64);
+        if (lane + o < 64) suf += t;
+      }
+      const unsigned long long higher = above + (suf - own);
+      if (higher < target && higher + own >= target) {
+        unsigned long long acc = higher;
+        for (int d = lane * c + c - 1; d >= lane * c; --d) {
+          if (acc + hist[d] >= target) {
+            s_sel[0] = (unsigned long long)d;
+            s_sel[1] = acc;
+            break;
+          }
+          acc += hist[d];
+        }
+      }
     }
   };
 
-  // first pass: Q and the top 11-bit digit (q >> 30) of every weight
-  for (int i = tid; i < 2048; i += NUC_THREADS) hist[i] = 0;
-  __syncthreads();
+  // first digit of every weight (a NaN has none, as a zero: w >= 1 fails), and Q
   unsigned long long Q = 0;
-  for_each_weight([&](float w) {
-    const unsigned long long q = (unsigned long long)w;
-    Q += q;
-    const int d = (int)(w * 0x1p-30f);  // truncation = floor (w >= 0)
-    if (d != 0) atomicAdd(&hist[d], q);
+  for_each_weight(-30.0f, INFINITY, [&](float w) {
+    if (w >= 1.0f) {
+      const unsigned long long q = (unsigned long long)w;
+      Q += q;
+      atomicAdd(&hist[min((__float_as_uint(w) - ONE) >> 18, (uint32_t)(BINS - 1))], q);
+    }
   });
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) Q += __shfl_xor(Q, o, 64);
@@ -318,75 +385,67 @@ __global__ __launch_bounds__(NUC_THREADS) void nucleus_kernel(const float* logit
   const unsigned __int128 prod = (unsigned __int128)mant * Q;  // < 2^82
   const unsigned long long target =
       sh >= 100 ? 1ull : (unsigned long long)((prod + (((unsigned __int128)1 << sh) - 1)) >> sh);
-
-  unsigned long long prefix = 0, above = 0, total = Q;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int shk = k == 0 ? 30 : k == 1 ? 19 : k == 2 ? 8 : 0, bk = k == 3 ? 8 : 11;
-    const int nb = 1 << bk;
-    if (k > 0) {  // histogram of digit k over the weights whose higher digits equal prefix
-      const float top_scale = __uint_as_float((uint32_t)(127 - shk - bk) << 23);  // 2^-(shk + bk)
-      const float dig_scale = __uint_as_float((uint32_t)(127 - shk) << 23);       // 2^-shk
-      const float pre_f = (float)prefix;  // exact: the prefix of an existing weight
-      const float base = (float)(1 << bk);
-      for_each_weight([&](float w) {
-        const float hi = floorf(w * top_scale);
-        if (hi == pre_f) {
-          const int d = (int)(floorf(w * dig_scale) - hi * base);
-          if (d != 0) atomicAdd(&hist[d], (unsigned long long)w);
-        }
+  select(BINS, 0, target);
+  __syncthreads();
+  uint32_t prefix = (uint32_t)s_sel[0];  // digits chosen so far, of the bits above ONE
+  unsigned long long above = s_sel[1];
+  if (tid == 0) {
+    // exp(y) 2^40 within half of the bin's weights (see y_in and y_out below)
+    const double lo = (double)__uint_as_float((prefix << 18) + ONE);
+    const double hi = (double)__uint_as_float(((prefix + 1) << 18) + ONE);
+    s_y[0] = (float)(log((lo - 0.5) * 0x1p-40) - 1e-4);
+    s_y[1] = (float)(log((hi + 0.5) * 0x1p-40) + 1e-4);
+  }
+  for (int i = tid; i < BINS; i += NUC_THREADS) hist[i] = 0;
+  __syncthreads();
+  // the boundary bin's weights, by their remaining 18 bits
+  const uint32_t bin = prefix;
+  const float y_lo = fmaxf(s_y[0], -30.0f), y_hi = s_y[1];
+  for_each_weight(y_lo, y_hi, [&](float w) {
+    const uint32_t k = __float_as_uint(w) - ONE;
+    if (w >= 1.0f && k >> 18 == bin) {
+      const int at = atomicAdd(&s_n, 1);
+      if (at < NUC_LIST) list[at] = k;
+    }
+  });
+  __syncthreads();
+  const int n = s_n;
+  auto for_each_left = [&](auto f) {  // f(bits of w above ONE) over the boundary bin
+    if (n <= NUC_LIST) {
+      for (int i = tid; i < n; i += NUC_THREADS) f(list[i]);
+    } else {
+      for_each_weight(y_lo, y_hi, [&](float w) {
+        const uint32_t k = __float_as_uint(w) - ONE;
+        if (w >= 1.0f && k >> 18 == bin) f(k);
       });
+    }
+  };
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    const int shk = pass == 0 ? 7 : 0, bk = pass == 0 ? 11 : 7;
+    for_each_left([&](uint32_t k) {
+      if (k >> (shk + bk) == prefix)
+        atomicAdd(&hist[(k >> shk) & ((1u << bk) - 1)], (unsigned long long)__uint_as_float(k + ONE));
+    });
+    __syncthreads();
+    select(1 << bk, above, target);
+    __syncthreads();
+    prefix = (prefix << bk) | (uint32_t)s_sel[0];
+    above = s_sel[1];
+    if (pass == 0) {
+      for (int i = tid; i < 128; i += NUC_THREADS) hist[i] = 0;
       __syncthreads();
     }
-    if (wave == 0) {  // lane l owns digits [l c, (l + 1) c); suffix sums over lanes, high to low
-      const int c = nb / 64;
-      unsigned long long own = 0;
-      for (int i = 0; i < c; ++i) own += hist[lane * c + i];
-      unsigned long long rest = own;  // digits 1.. of the pass
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) rest += __shfl_xor(rest, o, 64);
-      if (lane == 0) {  // digit 0 is the remainder of the pass's total
-        hist[0] = total - rest;
-        own += total - rest;
-      }
-      unsigned long long suf = own;  // sum over this lane's digits and every higher lane's
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const unsigned long long t = __shfl_down(suf, o, 64);
-        if (lane + o < 64) suf += t;
-      }
-      const unsigned long long higher = above + (suf - own);  // weight in digits above this lane's
-      if (higher < target && higher + own >= target) {
-        unsigned long long acc = higher;
-        for (int d = lane * c + c - 1; d >= lane * c; --d) {
-          if (acc + hist[d] >= target) {
-            s_sel[0] = (unsigned long long)d;
-            s_sel[1] = acc;
-            s_sel[2] = hist[d];
-            break;
-          }
-          acc += hist[d];
-        }
-      }
-    }
-    __syncthreads();
-    prefix = (prefix << bk) | s_sel[0];
-    above = s_sel[1];
-    total = s_sel[2];
-    if (k < 3) {
-      const int nb_next = k == 2 ? 256 : 2048;
-      for (int i = tid; i < nb_next; i += NUC_THREADS) hist[i] = 0;
-    }
-    __syncthreads();
   }
   if (tid == 0) {
     // exp(y) >= (tau + 1/2) 2^-40 e^(1e-4) makes the float32 weight round to >= tau; below
     // (tau - 1/2) 2^-40 e^(-1e-4) it rounds below tau (the float32 exponential and the
     // rounding of y = l' - m are within 1e-5 relative of exp(y))
-    const double t = (double)prefix;
+    const float tau = Q ? __uint_as_float(prefix + ONE) : 0.f;
+    const double t = (double)tau;
     const float y_in = (float)(log((t + 0.5) * 0x1p-40) + 1e-4);
     const float y_out = t > 0.5 ? (float)(log((t - 0.5) * 0x1p-40) - 1e-4) : -INFINITY;
-    thr[row] = NucleusThr{mx, y_in, y_out, 0, (long long)prefix};
+    thr[row] = NucleusThr{mx, y_in, y_out, 0, (long long)tau};
   }
 }
 
