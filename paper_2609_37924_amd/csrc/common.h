@@ -95,6 +95,28 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// Maximum / sum over each 16-lane row of the wave, every lane receiving it, by DPP (the
+// steps of wave_sum within a row).  The sum is exact where every partial sum is.
+__device__ __forceinline__ float row16_max(float v) {
+  v = fmaxf(v, dpp_f<0xB1>(v));
+  v = fmaxf(v, dpp_f<0x4E>(v));
+  v = fmaxf(v, dpp_f<0x141>(v));
+  return fmaxf(v, dpp_f<0x140>(v));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double(((long long)hi << 32) | (uint32_t)lo);
+}
+__device__ __forceinline__ double row16_sum(double v) {
+  v += dpp_d<0xB1>(v);
+  v += dpp_d<0x4E>(v);
+  v += dpp_d<0x141>(v);
+  return v + dpp_d<0x140>(v);
+}
+
 // Block-wide sum of one float per thread (blockDim.x a multiple of 64, <= 1024).
 __device__ __forceinline__ float block_sum(float v, float* red) {
   v = wave_sum(v);

@@ -115,26 +115,41 @@ __global__ __launch_bounds__(256) void sample_kernel(const float* logits, const 
         lp[e] = 4 * q + e < V ? l[u][e] * inv_temp : -INFINITY;
         mx = fmaxf(mx, lp[e]);
       }
+      mx = row16_max(mx);
+      // integer terms of at most 2^40, 64 of them a group: exact in float64
+      double sd = 0.0;
 #pragma unroll
-      for (int o = 1; o < 16; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-      long long sg = 0;
-      if (g < ng) {  // four integer terms below 2^41: exact in float64, converted once
-        double sd = 0.0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sd += (double)rintf(own_exp(lp[e] - mx) * 1099511627776.0f);  // * 2^40
-        sg = (long long)sd;
-      }
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) sg += __shfl_xor(sg, o, 64);
+      for (int e = 0; e < 4; ++e) sd += (double)rintf(own_exp_sel_2p40(lp[e] - mx));
+      sd = sd == sd ? sd : 0.0;  // four entries with a NaN among them add nothing
+      const long long sg = (long long)row16_sum(sd);
       if ((lane & 15) == 0 && g < ng) {
         s_S[g] = sg;
         s_m[g] = mx;
       }
       uint32_t ctr[4] = {(uint32_t)q, pos, (uint32_t)b, step_id};
       philox4x32_10(ctr, k0, k1);
+      if (nuc) {
+        // entries that are surely out take no part; the few whose weight has to be rounded
+        // to tell are told one at a time
+        bool unsure = false;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (4 * q + e < V && in_nucleus(lp[e])) top.add(screen_score(lp[e], uniform01(ctr[e])), 4 * q + e);
+        for (int e = 0; e < 4; ++e) unsure |= lp[e] - nm < y_in && lp[e] - nm >= y_out;
+        if (unsure) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (4 * q + e < V && in_nucleus(lp[e])) top.add(screen_score(lp[e], uniform01(ctr[e])), 4 * q + e);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool in = 4 * q + e < V && !(lp[e] - nm < y_out);
+            top.add(in ? screen_score(lp[e], uniform01(ctr[e])) : -INFINITY, 4 * q + e);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          top.add(4 * q + e < V ? screen_score(lp[e], uniform01(ctr[e])) : -INFINITY, 4 * q + e);
+      }
     }
   }
   __syncthreads();

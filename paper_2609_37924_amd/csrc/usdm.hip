@@ -107,42 +107,52 @@ __global__ __launch_bounds__(256) void entropy_kernel(const float* logits, int V
   // then converted once
   double Ad = 0.0, Bd = 0.0;
   Top2 top;
-  for (int q = tid; 4 * q < V; q += 256) {
-    float l[4];
-    if (vec) {
-      const float4 x = *reinterpret_cast<const float4*>(lg + 4 * q);
-      l[0] = x.x; l[1] = x.y; l[2] = x.z; l[3] = x.w;
-    } else {
+  constexpr int UNROLL = 4;  // granules whose loads are in flight together
+  for (int q0 = tid; 4 * q0 < V; q0 += 256 * UNROLL) {
+    float l[UNROLL][4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) l[e] = 4 * q + e < V ? lg[4 * q + e] : 0.f;
-    }
-    uint32_t c[4] = {(uint32_t)q, pos, (uint32_t)b, step_id};
-    philox4x32_10(c, k0, k1);
-    float w[4];
+    for (int u = 0; u < UNROLL; ++u) {
+      const int q = q0 + 256 * u;
+      if (vec) {
+        const float4 x = 4 * q < V ? *reinterpret_cast<const float4*>(lg + 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
+        l[u][0] = x.x; l[u][1] = x.y; l[u][2] = x.z; l[u][3] = x.w;
+      } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int v = 4 * q + e;
-      w[e] = 0.f;
-      if (v >= V) continue;
-      const float lp = l[e] * inv_temp;
-      const float y = lp - m;
-      const float ex = own_exp(y);
-      w[e] = ex;
-      Ad += (double)rintf(ex * TWO40);
-      Bd += ex > 0.f ? (double)rintf(((-y) * ex) * TWO40) : 0.0;
-      // the running top two, by selects
-      const float sc = screen_score(lp, uniform01(c[e]));
-      const bool t1 = sc > top.a1;
-      top.a2 = t1 ? top.a1 : fmaxf(top.a2, sc);
-      top.v1 = t1 ? v : top.v1;
-      top.a1 = t1 ? sc : top.a1;
+        for (int e = 0; e < 4; ++e) l[u][e] = 4 * q + e < V ? lg[4 * q + e] : 0.f;
+      }
     }
-    if (P) {
-      PT* dst = P + (size_t)row * ldp + 4 * q;
-      if (vec)
-        store4(dst, w[0], w[1], w[2], w[3]);
-      else
-        for (int e = 0; e < 4 && 4 * q + e < V; ++e) store_weight(dst + e, w[e]);
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      const int q = q0 + 256 * u;
+      if (4 * q >= V) break;
+      uint32_t c[4] = {(uint32_t)q, pos, (uint32_t)b, step_id};
+      philox4x32_10(c, k0, k1);
+      float w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int v = 4 * q + e;
+        w[e] = 0.f;
+        if (!vec && v >= V) continue;
+        const float lp = l[u][e] * inv_temp;
+        const float y = lp - m;
+        const float ex = own_exp_sel(y);
+        w[e] = ex;
+        Ad += (double)rintf(ex * TWO40);
+        Bd += ex > 0.f ? (double)rintf(((-y) * ex) * TWO40) : 0.0;
+        // the running top two, by selects
+        const float sc = screen_score(lp, uniform01(c[e]));
+        const bool t1 = sc > top.a1;
+        top.a2 = t1 ? top.a1 : fmaxf(top.a2, sc);
+        top.v1 = t1 ? v : top.v1;
+        top.a1 = t1 ? sc : top.a1;
+      }
+      if (P) {
+        PT* dst = P + (size_t)row * ldp + 4 * q;
+        if (vec)
+          store4(dst, w[0], w[1], w[2], w[3]);
+        else
+          for (int e = 0; e < 4 && 4 * q + e < V; ++e) store_weight(dst + e, w[e]);
+      }
     }
   }
   if (P)
