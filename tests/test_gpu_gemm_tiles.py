@@ -14,10 +14,11 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-def _model(d, vocab, B, P, G):
+def _model(d, vocab, B, P, G, base="small"):
     import paper_2609_37924_amd as tadm
-    cfg = synth.get_config("small", d_model=d, n_heads=d // 64, n_kv_heads=d // 64, d_ffn=64, vocab=vocab,
-                           n_anchor=0, n_denoise=0)
+    heads = dict(n_heads=d // 64, n_kv_heads=d // 64, d_ffn=64) if base == "small" else dict(
+        n_heads=d // 4, n_kv_heads=d // 4, head_dim=4, d_ffn=16)
+    cfg = synth.get_config(base, d_model=d, vocab=vocab, n_anchor=0, n_denoise=0, **heads)
     dev = torch.device("cuda:0")
     tensors = [t.to(dev) for t in synth.make_weights(cfg, perturb=True)]
     m = tadm.load_model(cfg, tensors, max_batch=B, max_seq=P + G, stream=torch.cuda.current_stream().cuda_stream)
@@ -29,7 +30,18 @@ def _model(d, vocab, B, P, G):
                                          (64, 300, 1, 63), (64, 516, 1, 1), (128, 1028, 1, 65), (320, 5000, 1, 129),
                                          (704, 96, 2, 33), (640, 3000, 3, 100)])
 def test_product_tiles(d, vocab, B, G):
-    tadm, cfg, dev, tensors, m = _model(d, vocab, B, 1, G)
+    _head_product(*_model(d, vocab, B, 1, G), d, vocab, B, G)
+
+
+@pytest.mark.parametrize("d,vocab,B,G", [(4, 4, 1, 1), (20, 12, 1, 17), (36, 100, 2, 15), (64, 256, 1, 24),
+                                         (132, 1028, 1, 33), (260, 516, 3, 16), (64, 4096, 1, 257)])
+def test_float32_product_tiles(d, vocab, B, G):
+    """float32 models: small products (16 x 16 tiles, K split over four waves, K not a multiple
+    of 16) and one beyond them."""
+    _head_product(*_model(d, vocab, B, 1, G, base="tiny"), d, vocab, B, G)
+
+
+def _head_product(tadm, cfg, dev, tensors, m, d, vocab, B, G):
     try:
         L = G + 1
         z = torch.randint(0, vocab, (B, L), dtype=torch.int32).to(dev)
