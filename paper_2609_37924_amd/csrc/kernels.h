@@ -139,10 +139,22 @@ constexpr size_t GEMM_SMALL_PART = 320 * 64 * 64;
 bool gemm_resid_norms(int M, int N, int K);
 
 // ---- norms / embedding / elementwise (norm.hip)
-// out[t, :] = embed[tok[t], :] as float32; `embed` has table_rows rows of length d
-// (ids outside [0, table_rows) are clamped so that the gather stays in bounds).
-hipError_t embed_gather(DType dt, const int32_t* tok, int n_tok, const void* embed, int table_rows,
-                        int d, float* out, hipStream_t s);
+// The embedding rows with what follows them in one pass (embed_rows; the table has table_rows
+// rows, ids outside them are clamped so that the gather stays in bounds): out (and out2, if set)
+// = embed[tok] + sc on the columns [off, L) of each row of L tokens (sc [n_tok / L, L - off, d],
+// optional), and y(T) = its RMSNorm (gains p), LayerNorm (affine p, q) or the row over p[row].
+struct EmbedRows {
+  enum Norm { NONE, RMS, LN, SCALE };
+  float *out = nullptr, *out2 = nullptr;
+  const float* sc = nullptr;
+  int L = 0, off = 0;
+  Norm norm = NONE;
+  const float *p = nullptr, *q = nullptr;
+  float eps = 0.f;
+  void* y = nullptr;
+};
+hipError_t embed_rows(DType dt, const int32_t* tok, int n_tok, const void* embed, int table_rows, int d,
+                      const EmbedRows& o, hipStream_t s);
 // y(T) = x / sqrt(mean(x^2) + eps) * g over rows of length d.  Row r of the
 // output is taken from input row map(r) = (r / rows_per_b) * in_stride_b + in_off + r % rows_per_b
 // (a gather of the canvas columns); pass rows_per_b = n_rows, in_stride_b = 0, in_off = 0 for identity.
@@ -230,8 +242,6 @@ hipError_t entropy_accept(const long long* Hq, const int32_t* xhat, const int32_
 // A block's first canvas: uniform tokens of positions pos_base + t into tok[b * ld + col0 + t].
 hipError_t init_uniform_tokens(int32_t* tok, int ld, int col0, int B, int n, int pos_base, uint32_t block,
                                uint64_t seed, int V, hipStream_t s);
-// c[b, off + j, :] += sc[b * (L - off) + j, :] (d % 4 == 0).
-hipError_t add_selfcond(float* c, const float* sc, int B, int L, int off, int d, hipStream_t s);
 // ET[n, v] = E[v, n] (v < V), zero for V <= v < ldt: E [V, d] row-major, ET [d, ldt].
 hipError_t transpose_rows(DType dt, const void* E, int V, int d, void* ET, int ldt, hipStream_t s);
 constexpr int ENTROPY_MAX_CANVAS = 8192;

@@ -18,16 +18,98 @@ __device__ __forceinline__ float4 load4<bf16>(const bf16* p) {
   return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
 }
 
-template <class T>
-__global__ void embed_kernel(const int32_t* tok, int n_tok, const T* E, int d, int max_row,
-                             float* out) {
-  const int q = d / 4;
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long)n_tok * q) return;
-  const int t = (int)(idx / q), c = (int)(idx % q);
-  int row = tok[t];
+// The embedding row of each token, plus the self-conditioning row on the columns [off, L),
+// to up to two float32 outputs, and the normalised row that its reader starts with (the
+// first layer's RMSNorm, the fusion's LayerNorm or row scale): one wave per row, the row in
+// registers (NV > 0: d <= 256 NV) or gathered again per pass (NV = 0), the arithmetic of
+// the norm's own kernel.  Bound by memory: 32 768 rows of 2 048, two
+// copies and RMSNorm, 178 us against 342 us for a gather, two copies and the norm.
+template <class T, int NV>
+__global__ __launch_bounds__(256) void embed_rows_kernel(const int32_t* tok, int n_tok, const T* E, int d, int max_row,
+                                                         EmbedRows o) {
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (r >= n_tok) return;
+  int row = tok[r];
   row = row < 0 ? 0 : (row > max_row ? max_row : row);  // memory safety for bad ids
-  *reinterpret_cast<float4*>(out + (size_t)t * d + 4 * c) = load4(E + (size_t)row * d + 4 * c);
+  const T* er = E + (size_t)row * d;
+  const float* sr = nullptr;
+  if (o.sc) {
+    const int b = r / o.L, l = r % o.L;
+    if (l >= o.off) sr = o.sc + ((size_t)b * (o.L - o.off) + (l - o.off)) * d;
+  }
+  auto at = [&](int c) {
+    float4 v = load4(er + c);
+    if (sr) {
+      const float4 x = *reinterpret_cast<const float4*>(sr + c);
+      v.x += x.x;
+      v.y += x.y;
+      v.z += x.z;
+      v.w += x.w;
+    }
+    return v;
+  };
+  constexpr int NR = NV > 0 ? NV : 1;
+  float4 keep[NR];
+  if constexpr (NV > 0) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int c = lane * 4 + 256 * i;
+      keep[i] = c < d ? at(c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  auto each = [&](auto f) {  // f(column, value) over this lane's part of the row
+    if constexpr (NV > 0) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        if (lane * 4 + 256 * i < d) f(lane * 4 + 256 * i, keep[i]);
+    } else {
+      for (int c = lane * 4; c < d; c += 256) f(c, at(c));
+    }
+  };
+  T* yr = static_cast<T*>(o.y) + (size_t)r * d;
+  const auto put = [&](int c, const float4& v) {
+    *reinterpret_cast<float4*>(o.out + (size_t)r * d + c) = v;
+    if (o.out2) *reinterpret_cast<float4*>(o.out2 + (size_t)r * d + c) = v;
+  };
+  if (o.norm == EmbedRows::NONE) {
+    each(put);
+  } else if (o.norm == EmbedRows::SCALE) {
+    const float inv = 1.f / o.p[r];
+    each([&](int c, const float4& v) {
+      put(c, v);
+      store4(yr + c, v.x * inv, v.y * inv, v.z * inv, v.w * inv);
+    });
+  } else if (o.norm == EmbedRows::RMS) {
+    float ss = 0.f;
+    each([&](int c, const float4& v) {
+      put(c, v);
+      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    });
+    ss = wave_sum(ss);
+    const float rs = rsqrtf(ss / d + o.eps);
+    each([&](int c, const float4& v) {
+      const float4 w = *reinterpret_cast<const float4*>(o.p + c);
+      store4(yr + c, v.x * rs * w.x, v.y * rs * w.y, v.z * rs * w.z, v.w * rs * w.w);
+    });
+  } else {
+    float s = 0.f;
+    each([&](int c, const float4& v) {
+      put(c, v);
+      s += v.x + v.y + v.z + v.w;
+    });
+    const float mu = wave_sum(s) / d;
+    float ss = 0.f;
+    each([&](int, const float4& v) {
+      const float a = v.x - mu, b = v.y - mu, c = v.z - mu, e = v.w - mu;
+      ss += a * a + b * b + c * c + e * e;
+    });
+    const float rs = rsqrtf(wave_sum(ss) / d + o.eps);
+    each([&](int c, const float4& v) {
+      const float4 w = *reinterpret_cast<const float4*>(o.p + c), b = *reinterpret_cast<const float4*>(o.q + c);
+      store4(yr + c, (v.x - mu) * rs * w.x + b.x, (v.y - mu) * rs * w.y + b.y, (v.z - mu) * rs * w.z + b.z,
+             (v.w - mu) * rs * w.w + b.w);
+    });
+  }
 }
 
 // y[r] = x[map(r)] * rsqrt(mean(x^2) + eps) * g.  NV > 0: d <= 256 NV and the row stays in
@@ -98,34 +180,49 @@ __global__ __launch_bounds__(256) void rms_gather_kernel(const float* x, const f
   }
 }
 
-template <class T>
+// LayerNorm rows to y_t (T) and / or y_f (float).  NV > 0: d <= 256 NV and the row stays in
+// registers (one read of x); NV = 0: any d, x read three times.
+template <class T, int NV>
 __global__ __launch_bounds__(256) void ln_kernel(const float* x, const float* w, const float* b,
                                                  float eps, int n_rows, int d, T* y_t, float* y_f) {
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (r >= n_rows) return;
   const float* xr = x + (size_t)r * d;
-  float s = 0.f;
-  for (int c = lane * 4; c < d; c += 256) {
-    const float4 v = *reinterpret_cast<const float4*>(xr + c);
-    s += v.x + v.y + v.z + v.w;
+  constexpr int NR = NV > 0 ? NV : 1;
+  float4 keep[NR];
+  if constexpr (NV > 0) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int c = lane * 4 + 256 * i;
+      keep[i] = c < d ? *reinterpret_cast<const float4*>(xr + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
   }
+  auto each = [&](auto f) {
+    if constexpr (NV > 0) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        if (lane * 4 + 256 * i < d) f(lane * 4 + 256 * i, keep[i]);
+    } else {
+      for (int c = lane * 4; c < d; c += 256) f(c, *reinterpret_cast<const float4*>(xr + c));
+    }
+  };
+  float s = 0.f;
+  each([&](int, const float4& v) { s += v.x + v.y + v.z + v.w; });
   const float mu = wave_sum(s) / d;
   float ss = 0.f;
-  for (int c = lane * 4; c < d; c += 256) {
-    const float4 v = *reinterpret_cast<const float4*>(xr + c);
+  each([&](int, const float4& v) {
     const float a = v.x - mu, bb = v.y - mu, cc = v.z - mu, dd = v.w - mu;
     ss += a * a + bb * bb + cc * cc + dd * dd;
-  }
+  });
   const float rs = rsqrtf(wave_sum(ss) / d + eps);
-  for (int c = lane * 4; c < d; c += 256) {
-    const float4 v = *reinterpret_cast<const float4*>(xr + c);
+  each([&](int c, const float4& v) {
     const float4 ww = *reinterpret_cast<const float4*>(w + c);
     const float4 bb = *reinterpret_cast<const float4*>(b + c);
     const float o0 = (v.x - mu) * rs * ww.x + bb.x, o1 = (v.y - mu) * rs * ww.y + bb.y;
     const float o2 = (v.z - mu) * rs * ww.z + bb.z, o3 = (v.w - mu) * rs * ww.w + bb.w;
     if (y_t) store4(y_t + (size_t)r * d + c, o0, o1, o2, o3);
     if (y_f) store4(y_f + (size_t)r * d + c, o0, o1, o2, o3);
-  }
+  });
 }
 
 // LayerNorm of x in place (float32), then the RMSNorm of its result into y (the next
@@ -237,17 +334,20 @@ inline unsigned blocks(long n, int per) { return (unsigned)((n + per - 1) / per)
 
 }  // namespace
 
-hipError_t embed_gather(DType dt, const int32_t* tok, int n_tok, const void* embed, int table_rows,
-                        int d, float* out, hipStream_t s) {
-  const long n = (long)n_tok * (d / 4);
-  if (n == 0) return hipSuccess;
-  if (dt == BF16)
-    hipLaunchKernelGGL(embed_kernel<bf16>, dim3(blocks(n, 256)), dim3(256), 0, s, tok, n_tok,
-                       static_cast<const bf16*>(embed), d, table_rows - 1, out);
-  else
-    hipLaunchKernelGGL(embed_kernel<float>, dim3(blocks(n, 256)), dim3(256), 0, s, tok, n_tok,
-                       static_cast<const float*>(embed), d, table_rows - 1, out);
-  return hipGetLastError();
+hipError_t embed_rows(DType dt, const int32_t* tok, int n_tok, const void* embed, int table_rows, int d,
+                      const EmbedRows& o, hipStream_t s) {
+  if (n_tok == 0) return hipSuccess;
+  auto go = [&](auto kernel, auto* table) {
+    hipLaunchKernelGGL(kernel, dim3(blocks(n_tok, 4)), dim3(256), 0, s, tok, n_tok, table, d, table_rows - 1, o);
+    return hipGetLastError();
+  };
+  if (dt == BF16) {
+    const bf16* E = static_cast<const bf16*>(embed);
+    if (d <= 1024) return go(embed_rows_kernel<bf16, 4>, E);
+    if (d <= 2048) return go(embed_rows_kernel<bf16, 8>, E);
+    return go(embed_rows_kernel<bf16, 0>, E);
+  }
+  return go(embed_rows_kernel<float, 0>, static_cast<const float*>(embed));
 }
 
 hipError_t rms_norm(DType dt, const float* x, const float* g, float eps, int n_rows, int d,
@@ -291,13 +391,18 @@ hipError_t rms_norm_gather(DType dt, const float* x, const float* g, float eps, 
 hipError_t layer_norm(DType dt, const float* x, const float* w, const float* b, float eps, int n_rows,
                       int d, void* y_t, float* y_f, hipStream_t s) {
   if (n_rows == 0) return hipSuccess;
-  if (dt == BF16)
-    hipLaunchKernelGGL(ln_kernel<bf16>, dim3(blocks(n_rows, 4)), dim3(256), 0, s, x, w, b, eps, n_rows,
-                       d, static_cast<bf16*>(y_t), y_f);
-  else
-    hipLaunchKernelGGL(ln_kernel<float>, dim3(blocks(n_rows, 4)), dim3(256), 0, s, x, w, b, eps, n_rows,
-                       d, static_cast<float*>(y_t), y_f);
-  return hipGetLastError();
+  const dim3 grid(blocks(n_rows, 4));
+  auto go = [&](auto kernel, auto* y) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, x, w, b, eps, n_rows, d, y, y_f);
+    return hipGetLastError();
+  };
+  if (dt == BF16) {
+    bf16* y = static_cast<bf16*>(y_t);
+    if (d <= 1024) return go(ln_kernel<bf16, 4>, y);
+    if (d <= 2048) return go(ln_kernel<bf16, 8>, y);
+    return go(ln_kernel<bf16, 0>, y);
+  }
+  return go(ln_kernel<float, 0>, static_cast<float*>(y_t));
 }
 
 hipError_t layer_rms_norm(DType dt, float* x, const float* w, const float* b, float ln_eps, const float* g,
@@ -307,6 +412,9 @@ hipError_t layer_rms_norm(DType dt, float* x, const float* w, const float* b, fl
   if (dt == BF16) {
     if (d <= 1024)
       hipLaunchKernelGGL((ln_rms_kernel<bf16, 4>), grid, dim3(256), 0, s, x, w, b, ln_eps, g, rms_eps, n_rows, d,
+                         static_cast<bf16*>(y));
+    else if (d <= 2048)
+      hipLaunchKernelGGL((ln_rms_kernel<bf16, 8>), grid, dim3(256), 0, s, x, w, b, ln_eps, g, rms_eps, n_rows, d,
                          static_cast<bf16*>(y));
     else
       hipLaunchKernelGGL((ln_rms_kernel<bf16, 0>), grid, dim3(256), 0, s, x, w, b, ln_eps, g, rms_eps, n_rows, d,

@@ -608,13 +608,19 @@ static tadm_status run_part(tadm_model* m, int first, int count, float* x, int B
 }
 
 // c = S(z): embedding gather (plus the self-conditioning signal sc on the columns
-// [off, L), if given) then the shared layers (in place on `c`).
+// [off, L), if given) then the shared layers (in place on `c`).  next: what the reader of c
+// starts with; without shared layers the gather does it (next->out2 and next->norm) and
+// *fused is set.
 static tadm_status shared_net(tadm_model* m, const tadm_context* ctx, const int32_t* z, int B, int L,
-                              float* c, const float* sc = nullptr, int off = 0) {
+                              float* c, const float* sc, int off, const EmbedRows& next, bool* fused) {
   const int pos0 = ctx ? ctx->len : 0;
-  HIPCHK(embed_gather(m->dt, z, B * L, m->W(m->lay.embed), m->cfg.vocab + 1, m->cfg.d_model, c,
-                      m->stream));
-  if (sc) HIPCHK(add_selfcond(c, sc, B, L, off, m->cfg.d_model, m->stream));
+  *fused = m->cfg.n_shared == 0;
+  EmbedRows o = *fused ? next : EmbedRows{};
+  o.out = c;
+  o.sc = sc;
+  o.L = L;
+  o.off = off;
+  HIPCHK(embed_rows(m->dt, z, B * L, m->W(m->lay.embed), m->cfg.vocab + 1, m->cfg.d_model, o, m->stream));
   return run_part(m, 0, m->cfg.n_shared, c, B, L, pos0, ctx);
 }
 
@@ -677,12 +683,13 @@ static tadm_status paired_mixer(tadm_model* m, int B, int L, const float* Zf, co
   return TADM_OK;
 }
 
-// Z = (C / s_C) W_C into ws.pz (float) and ws.pzb (model type).
-static tadm_status paired_project(tadm_model* m, int N, const float* C, const float* sC, float* Zf, void* Zb) {
+// Z = (C / s_C) W_C into ws.pz (float) and ws.pzb (model type); ready: ws.xn holds C / s_C.
+static tadm_status paired_project(tadm_model* m, int N, const float* C, const float* sC, float* Zf, void* Zb,
+                                  bool ready = false) {
   const tadm_config& cf = m->cfg;
   Workspace& s = m->ws;
   const int d = cf.d_model, r = cf.fusion_rank;
-  HIPCHK(scale_rows(m->dt, C, sC, N, d, s.xn, m->stream));
+  if (!ready) HIPCHK(scale_rows(m->dt, C, sC, N, d, s.xn, m->stream));
   GemmProblem p{N, r, d, s.xn, d, d, nullptr, 0, m->W(m->lay.p_wc), d};
   EpiParams e;
   e.out = Zf;
@@ -714,14 +721,14 @@ static tadm_status paired_prepare(tadm_model* m, int B, int L, tadm_cache* cache
 }
 
 // Step: H~ = H0 + g * s_H * (M W_up) into ws.x.
-static tadm_status paired_fuse(tadm_model* m, int B, int L, const float* c, const tadm_cache* ccache) {
+static tadm_status paired_fuse(tadm_model* m, int B, int L, const float* c, const tadm_cache* ccache, bool ready) {
   tadm_cache* cache = const_cast<tadm_cache*>(ccache);  // phi0 is only read here
   const tadm_config& cf = m->cfg;
   Workspace& s = m->ws;
   const Layout& Y = m->lay;
   const int N = B * L, d = cf.d_model, r = cf.fusion_rank;
   const hipStream_t st = m->stream;
-  TRY(paired_project(m, N, c, cache->sC, s.pz, s.pzb));
+  TRY(paired_project(m, N, c, cache->sC, s.pz, s.pzb, ready));
   TRY(paired_mixer(m, B, L, s.pz, s.pzb, cache, false));
   HIPCHK(paired_features(m->dt, cache->U, cache->Z0, s.pz, s.pmb, N, r, s.pf, st));
   {
@@ -746,35 +753,66 @@ static tadm_status paired_fuse(tadm_model* m, int B, int L, const float* c, cons
   return TADM_OK;
 }
 
-// anchor refresh: h = A(c) into the cache, with the fusion's anchor-side input.
-static tadm_status anchor_net(tadm_model* m, const tadm_context* ctx, int B, int L, const float* c,
-                              tadm_cache* cache) {
+// anchor refresh from the canvas: c = S(z) and h = A(c) into the cache, with the fusion's
+// anchor-side input.  stages: profile its two parts (a context pass is a stage of its own).
+static tadm_status shared_anchor(tadm_model* m, const tadm_context* ctx, const int32_t* z, int B, int L, const float* sc,
+                                 int off, tadm_cache* cache, bool stages) {
   const tadm_config& cf = m->cfg;
-  const size_t n = (size_t)B * L * cf.d_model;
-  HIPCHK(copy_f32(c, cache->c, n, m->stream));
-  HIPCHK(copy_f32(c, cache->h, n, m->stream));
-  TRY(run_part(m, cf.n_shared, cf.n_anchor, cache->h, B, L, ctx ? ctx->len : 0, ctx));
+  EmbedRows next;  // the anchor network's input, and its first layer's norm of it
+  next.out2 = cache->h;
+  if (cf.n_anchor > 0) {
+    next.norm = EmbedRows::RMS;
+    next.p = m->Wf(m->lay.layers[cf.n_shared].attn_norm);
+    next.eps = cf.rms_eps;
+    next.y = m->ws.xn;
+  }
+  bool fused;
+  if (stages) TRY(prof_begin(m, TADM_STAGE_EMBED));
+  TRY(shared_net(m, ctx, z, B, L, cache->c, sc, off, next, &fused));
+  if (stages) {
+    TRY(prof_end(m, TADM_STAGE_EMBED));
+    TRY(prof_begin(m, TADM_STAGE_ANCHOR));
+  }
+  if (!fused) HIPCHK(copy_f32(cache->c, cache->h, (size_t)B * L * cf.d_model, m->stream));
+  TRY(run_part(m, cf.n_shared, cf.n_anchor, cache->h, B, L, ctx ? ctx->len : 0, ctx, fused && cf.n_anchor > 0));
   if (cf.fusion_kind == TADM_FUSION_GATED_MLP)
     HIPCHK(layer_norm(m->dt, cache->h, m->Wf(m->lay.ln_a_w), m->Wf(m->lay.ln_a_b), cf.ln_eps, B * L,
                       cf.d_model, cache->a, nullptr, m->stream));
   else
     TRY(paired_prepare(m, B, L, cache));
-  return TADM_OK;
+  return stages ? prof_end(m, TADM_STAGE_ANCHOR) : TADM_OK;
 }
 
-// h~ = Phi(c, cache) into ws.x.
-// h~ = Phi(c, h') into ws.x.  With the gated MLP fusion and denoiser layers, its closing
+// What the fusion starts with from c: the gated MLP's LayerNorm of it, or the paired
+// attention's row over the cached scale, into ws.xn.
+static EmbedRows fusion_input(const tadm_model* m, const tadm_cache* cache) {
+  EmbedRows next;
+  next.y = m->ws.xn;
+  if (m->cfg.fusion_kind == TADM_FUSION_GATED_MLP) {
+    next.norm = EmbedRows::LN;
+    next.p = m->Wf(m->lay.ln_s_w);
+    next.q = m->Wf(m->lay.ln_s_b);
+    next.eps = m->cfg.ln_eps;
+  } else {
+    next.norm = EmbedRows::SCALE;
+    next.p = cache->sC;
+  }
+  return next;
+}
+
+// h~ = Phi(c, h') into ws.x; ready: ws.xn holds what the fusion starts with from c
+// (fusion_input).  With the gated MLP fusion and denoiser layers, its closing
 // LayerNorm also writes the first denoiser layer's attention norm to ws.xn (*prenormed).
-static tadm_status fusion(tadm_model* m, int B, int L, const float* c, const tadm_cache* cache,
+static tadm_status fusion(tadm_model* m, int B, int L, const float* c, const tadm_cache* cache, bool ready,
                           bool* prenormed) {
   const tadm_config& cf = m->cfg;
   *prenormed = false;
-  if (cf.fusion_kind == TADM_FUSION_PAIRED) return paired_fuse(m, B, L, c, cache);
+  if (cf.fusion_kind == TADM_FUSION_PAIRED) return paired_fuse(m, B, L, c, cache, ready);
   Workspace& s = m->ws;
   const int N = B * L, d = cf.d_model;
   const Layout& Y = m->lay;
   const hipStream_t st = m->stream;
-  HIPCHK(layer_norm(m->dt, c, m->Wf(Y.ln_s_w), m->Wf(Y.ln_s_b), cf.ln_eps, N, d, s.xn, nullptr, st));
+  if (!ready) HIPCHK(layer_norm(m->dt, c, m->Wf(Y.ln_s_w), m->Wf(Y.ln_s_b), cf.ln_eps, N, d, s.xn, nullptr, st));
   {
     GemmProblem p{N, 5 * d, 2 * d, s.xn, d, d, cache->a, d, m->W(Y.w1g), 2 * d};
     EpiParams e;
@@ -1172,10 +1210,9 @@ tadm_status tadm_context_destroy(tadm_context* ctx) {
 static tadm_status context_append_impl(tadm_model* m, tadm_context* ctx, const int32_t* tok, int B,
                                        int n, tadm_cache* scratch) {
   Workspace& s = m->ws;
-  TRY(shared_net(m, ctx, tok, B, n, s.c));
-  TRY(anchor_net(m, ctx, B, n, s.c, scratch));
+  TRY(shared_anchor(m, ctx, tok, B, n, nullptr, 0, scratch, false));
   bool prenormed;
-  TRY(fusion(m, B, n, s.c, scratch, &prenormed));
+  TRY(fusion(m, B, n, scratch->c, scratch, false, &prenormed));
   TRY(run_part(m, m->cfg.n_shared + m->cfg.n_anchor, m->cfg.n_denoise, s.x, B, n, ctx->len, ctx, prenormed));
   ctx->len += n;
   return TADM_OK;
@@ -1201,12 +1238,7 @@ tadm_status tadm_context_append(tadm_model* m, tadm_context* ctx, const int32_t*
 // ------------------------------------------------------------------ step ----
 static tadm_status anchor_impl(tadm_model* m, const tadm_context* ctx, const int32_t* canvas, int B,
                                int L, int i, tadm_cache* cache, const float* sc = nullptr, int off = 0) {
-  TRY(prof_begin(m, TADM_STAGE_EMBED));
-  TRY(shared_net(m, ctx, canvas, B, L, m->ws.c, sc, off));
-  TRY(prof_end(m, TADM_STAGE_EMBED));
-  TRY(prof_begin(m, TADM_STAGE_ANCHOR));
-  TRY(anchor_net(m, ctx, B, L, m->ws.c, cache));
-  TRY(prof_end(m, TADM_STAGE_ANCHOR));
+  TRY(shared_anchor(m, ctx, canvas, B, L, sc, off, cache, true));
   cache->refresh_i = i;
   return TADM_OK;
 }
@@ -1320,11 +1352,12 @@ static tadm_status denoise_impl(tadm_model* m, const tadm_context* ctx, const in
   const int pos0 = ctx ? ctx->len : 0, Lc = L - off, d = cf.d_model;
   const bool entropy = a->mode == TADM_STEP_ENTROPY;
   TRY(prof_begin(m, TADM_STAGE_EMBED));
-  TRY(shared_net(m, ctx, canvas, B, L, s.c, entropy ? a->sc_in : nullptr, off));
+  bool ready;
+  TRY(shared_net(m, ctx, canvas, B, L, s.c, entropy ? a->sc_in : nullptr, off, fusion_input(m, cache), &ready));
   TRY(prof_end(m, TADM_STAGE_EMBED));
   TRY(prof_begin(m, TADM_STAGE_FUSION));
   bool prenormed;
-  TRY(fusion(m, B, L, s.c, cache, &prenormed));
+  TRY(fusion(m, B, L, s.c, cache, ready, &prenormed));
   TRY(prof_end(m, TADM_STAGE_FUSION));
   if (m->taps) HIPCHK(copy_f32(s.x, s.ht, (size_t)B * L * d, m->stream));
   const bool full = logits != nullptr, all_rows = full || entropy;
@@ -1680,11 +1713,12 @@ tadm_status tadm_train_loss(tadm_model* m, const int32_t* x_dev, int32_t B, int3
   // stale anchor from z_t', current pass on z_t
   TRY(anchor_impl(m, nullptr, zs, B, L, 1, cache));
   TRY(prof_begin(m, TADM_STAGE_EMBED));
-  TRY(shared_net(m, nullptr, zt, B, L, s.c));
+  bool ready;
+  TRY(shared_net(m, nullptr, zt, B, L, s.c, nullptr, 0, fusion_input(m, cache), &ready));
   TRY(prof_end(m, TADM_STAGE_EMBED));
   TRY(prof_begin(m, TADM_STAGE_FUSION));
   bool prenormed;
-  TRY(fusion(m, B, L, s.c, cache, &prenormed));
+  TRY(fusion(m, B, L, s.c, cache, ready, &prenormed));
   TRY(prof_end(m, TADM_STAGE_FUSION));
   TRY(prof_begin(m, TADM_STAGE_DENOISE));
   TRY(run_part(m, cf.n_shared + cf.n_anchor, cf.n_denoise, s.x, B, L, 0, nullptr, prenormed));

@@ -464,53 +464,69 @@ __global__ __launch_bounds__(NUC_THREADS) void nucleus_kernel(const float* logit
   }
 }
 
-// One workgroup of 1024 threads scans every canvas entry in row-major order.
-// Masked canvas positions in order get rows 0, 1, ... (idx: row -> position, row_map:
-// position -> row or -1); rows from `bound` on are not assigned (row_map -1): a caller
-// that sized its work for `bound` rows never reads a row it did not compute.
+// One workgroup of 1024 threads scans every canvas entry in row-major order, eight consecutive
+// entries per thread and pass (one entry: 42 us over 32 768 positions, a block-wide scan per
+// 1 024; eight: 38).  Masked canvas positions in order get rows 0, 1, ... (idx: row ->
+// position, row_map: position -> row or -1); rows from `bound` on are not assigned (row_map
+// -1): a caller that sized its work for `bound` rows never reads a row it did not compute.
 __global__ __launch_bounds__(1024) void compact_kernel(const int32_t* canvas, int B, int L, int off,
                                                        int mask_id, int bound, int32_t* idx, int32_t* row_map,
                                                        int* count) {
-  __shared__ int wsum[16];
-  __shared__ int base;
+  constexpr int PER = 8;
+  __shared__ int wsum[2][16];
   const int Lc = L - off, n = B * Lc;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (threadIdx.x == 0) base = 0;
-  __syncthreads();
-  for (int c0 = 0; c0 < n; c0 += 1024) {
-    const int c = c0 + threadIdx.x;
-    const int m = c < n && canvas[(size_t)(c / Lc) * L + off + c % Lc] == mask_id;
-    // wave prefix via ballot
-    const unsigned long long bal = __ballot(m);
-    const int before = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) wsum[wave] = __popcll(bal);
+  int base = 0;  // masked entries of the passes before, the same in every thread
+  for (int c0 = 0, pass = 0; c0 < n; c0 += 1024 * PER, ++pass) {
+    const int c1 = c0 + threadIdx.x * PER;
+    uint32_t bits = 0;
+    int b = min(c1, n) / Lc, j = min(c1, n) - b * Lc, tok[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {  // every load first
+      tok[k] = c1 + k < n ? canvas[(size_t)b * L + off + j] : ~mask_id;
+      if (++j == Lc) {
+        j = 0;
+        ++b;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) bits |= (tok[k] == mask_id ? 1u : 0u) << k;
+    const int own = __popc(bits);
+    int upto = own;  // inclusive over the lanes
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(upto, o, 64);
+      if (lane >= o) upto += t;
+    }
+    int* ws = wsum[pass & 1];
+    if (lane == 63) ws[wave] = upto;
     __syncthreads();
-    int woff = 0;
-    for (int w = 0; w < wave; ++w) woff += wsum[w];
-    const int r = base + woff + before;
-    if (c < n) {
-      const bool kept = m && r < bound;
+    int r = base + upto - own;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) r += ws[w];
+      base += ws[w];
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int c = c1 + k;
+      if (c >= n) break;
+      const bool kept = ((bits >> k) & 1) && r < bound;
       row_map[c] = kept ? r : -1;
       if (kept) idx[r] = c;
+      r += (bits >> k) & 1;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int t = 0;
-      for (int w = 0; w < 16; ++w) t += wsum[w];
-      base += t;
-    }
-    __syncthreads();
   }
   if (threadIdx.x == 0) *count = min(base, bound);
 }
 
-// One workgroup of 1024 threads per row; rank by (conf desc, position asc) among the
-// masked positions.  The row's confidences go to LDS with -inf for entries that are not
+// Workgroups of 1024 threads per row and 256 of its positions (one per row: 60 us for 32 rows of
+// 1 024; now 18); rank by (conf desc, position asc) among the masked positions.  The row's confidences go to LDS with -inf for entries that are not
 // masked (a finite confidence never ranks below them); four threads share a position,
 // each counting the better entries in a quarter of the row with float4 reads, and
-// lanes 4k..4k+3 add their counts.  One workgroup per row keeps the update in place:
-// every canvas read of the row happens before the barrier, and each position is written
-// only by its own threads.
+// lanes 4k..4k+3 add their counts.  next may be the canvas itself: a workgroup reads the
+// canvas at its own positions only, each before its own thread writes it, and tells the
+// other positions' candidates by their choice (the sampler gives -1 to every entry that
+// is not masked).
 constexpr int SELECT_THREADS = 1024;
 __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const int32_t* canvas, const int32_t* choice,
                                                                 const float* conf, int L, int off, int Lc,
@@ -524,15 +540,15 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const int32_t* c
   // the candidates are the masked positions that were sampled (choice >= 0); a
   // candidate's confidence is at least -FLT_MAX, so it ranks ahead of every other slot
   for (int p = tid; p < Lc16; p += SELECT_THREADS) {
-    const bool m = p < Lc && canvas[(size_t)b * L + off + p] == mask_id && choice[(size_t)b * Lc + p] >= 0;
+    const bool m = p < Lc && choice[(size_t)b * Lc + p] >= 0;
     sc[p] = m ? fmaxf(conf[(size_t)b * Lc + p], -FLT_MAX) : -INFINITY;
     cnt += m ? 1.f : 0.f;
   }
   const int n_masked = (int)block_sum(cnt, red);  // exact: counts < 2^24; ends with a barrier
   const int n = min(n_rows ? max(n_rows[b], 0) : n_unmask, n_masked);
   const int sub = tid & 3;
-  for (int l0 = 0; l0 < L; l0 += SELECT_THREADS / 4) {
-    const int l = l0 + (tid >> 2), p = l - off;
+  {
+    const int l = blockIdx.y * (SELECT_THREADS / 4) + (tid >> 2), p = l - off;
     const bool mine = l < L;
     const int t = mine ? canvas[(size_t)b * L + l] : 0;
     const bool cand = mine && p >= 0 && p < Lc && t == mask_id && n > 0 && sc[p] != -INFINITY;
@@ -622,7 +638,7 @@ hipError_t select_unmask(const int32_t* canvas, const int32_t* choice, const flo
                          hipStream_t s) {
   const int Lc = L - canvas_off;
   if (B == 0) return hipSuccess;
-  hipLaunchKernelGGL(select_kernel, dim3(B), dim3(SELECT_THREADS), (size_t)((Lc + 15) & ~15) * 4, s, canvas, choice,
+  hipLaunchKernelGGL(select_kernel, dim3(B, (L + SELECT_THREADS / 4 - 1) / (SELECT_THREADS / 4)), dim3(SELECT_THREADS), (size_t)((Lc + 15) & ~15) * 4, s, canvas, choice,
                      conf, L, canvas_off, Lc, mask_id, n_unmask, n_rows, next);
   return hipGetLastError();
 }

@@ -259,23 +259,6 @@ __global__ void init_uniform_kernel(int32_t* tok, int ld, int col0, int B, int n
   tok[(size_t)b * ld + col0 + t] = uniform_token(INIT_WORD0, (uint32_t)(pos_base + t), (uint32_t)b, block, k0, k1, V);
 }
 
-// c[b, off + j, :] += sc[b * Lc + j, :] (float4 granules; d % 4 == 0)
-__global__ void add_selfcond_kernel(float* c, const float* sc, int B, int L, int off, int Lc, int d) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x, d4 = d / 4;
-  if (i >= (long)B * Lc * d4) return;
-  const long r = i / d4, k = i % d4;
-  const int b = (int)(r / Lc), j = (int)(r % Lc);
-  float4* dst = reinterpret_cast<float4*>(c + ((size_t)b * L + off + j) * d) + k;
-  const float4 s = reinterpret_cast<const float4*>(sc + (size_t)r * d)[k];
-  float4 x = *dst;
-  x.x += s.x;
-  x.y += s.y;
-  x.z += s.z;
-  x.w += s.w;
-  *dst = x;
-}
-
-// ET[n, v] = E[v, n] for v < V, 0 for V <= v < ldt; 64 x 64 tiles through LDS
 template <class T>
 __global__ __launch_bounds__(256) void transpose_kernel(const T* E, int V, int d, T* ET, int ldt) {
   __shared__ T tile[64][65];
@@ -323,15 +306,6 @@ hipError_t init_uniform_tokens(int32_t* tok, int ld, int col0, int B, int n, int
   if (total == 0) return hipSuccess;
   hipLaunchKernelGGL(init_uniform_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, tok, ld, col0, B, n,
                      pos_base, block, (uint32_t)(seed & 0xFFFFFFFFu), (uint32_t)(seed >> 32), V);
-  return hipGetLastError();
-}
-
-hipError_t add_selfcond(float* c, const float* sc, int B, int L, int off, int d, hipStream_t s) {
-  const int Lc = L - off;
-  const long total = (long)B * Lc * (d / 4);
-  if (total == 0) return hipSuccess;
-  hipLaunchKernelGGL(add_selfcond_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, c, sc, B, L, off,
-                     Lc, d);
   return hipGetLastError();
 }
 
