@@ -8,7 +8,7 @@
 //
 // This file is compiled with -ffp-contract=off and correctly rounded float32 division
 // (the contract arithmetic of sampler_math.h); the MFMA main loop is unaffected.
-#include "gemm_kernel.h"
+#include "gemm_tall.h"
 #include "sampler_math.h"
 
 namespace tadm {
@@ -32,29 +32,31 @@ template <class T>
 struct Epi<EPI_SAMPLE, T> {
   static constexpr bool kTile = true;
 
-  // acc[a][b][jj] = C[n = nb + 16 a + 4 (lane >> 4) + jj][m = mb + 16 b + (lane & 15)]
-  template <int TN, int TM>
+  // acc[a][b][jj] = C[n = nb + 16 a + 4 (lane >> 4) + jj][m = mb + 16 b + (lane & 15)], with GAP
+  // rows more from row subtile TM / 2 on
+  template <int TN, int TM, int GAP = 0>
   __device__ __forceinline__ static void tile(const EpiParams& e, const GemmProblem& p, const f32x4 (&acc)[TN][TM],
-                                              int mb,
-                              int nb, int lane) {
+                                              int mb, int nb, int lane) {
     static_assert(TN * 16 == SAMPLE_GROUP, "one wave column strip must be one normaliser group");
     const int fr = lane & 15, fq = lane >> 4;
     const int g = nb / SAMPLE_GROUP;
-    f32x4 rot[TN][TM];  // row subtile b in rot[.][0]: the others move down one place per pass
-#pragma unroll
-    for (int a = 0; a < TN; ++a)
-#pragma unroll
-      for (int k = 0; k < TM; ++k) rot[a][k] = acc[a][k];
 #pragma unroll 1
     for (int b = 0; b < TM; ++b) {
+      const int mrow = mb + 16 * b + (b >= TM / 2 ? GAP : 0);
+      if (mrow >= p.M) break;  // no row of this subtile, nor of the later ones
+      // row subtile b, by uniform branches: each is read with static indices (a runtime index
+      // into acc would move the whole tile to scratch, and selects cost more)
       f32x4 cb[TN];
 #pragma unroll
-      for (int a = 0; a < TN; ++a) {
-        cb[a] = rot[a][0];
+      for (int a = 0; a < TN; ++a) cb[a] = acc[a][0];
 #pragma unroll
-        for (int k = 1; k < TM; ++k) rot[a][k - 1] = rot[a][k];
-      }
-      const int m = mb + 16 * b + fr;
+      for (int k = 1; k < TM; ++k)
+        if (b == k) {
+          asm volatile("; row subtile" :::);  // keeps the branch from becoming selects
+#pragma unroll
+          for (int a = 0; a < TN; ++a) cb[a] = acc[a][k];
+        }
+      const int m = mrow + fr;
       const bool row_ok = m < p.M;
       const int ci = e.rows_idx[row_ok ? m : 0];
       const uint32_t brow = (uint32_t)(ci / e.Lc), pos = (uint32_t)(e.pos_base + ci % e.Lc);
@@ -79,14 +81,14 @@ struct Epi<EPI_SAMPLE, T> {
       int v1 = 0x7FFFFFFF;
       // one vocabulary entry; the first loop is for strips wholly inside the vocabulary
       auto entry = [&](float l, float u, int v) {
-        S += (double)rintf(own_exp_sel_2p40(l - mx));
+        S += (double)own_exp_term(l - mx);
         const float sc = screen_score(l, u);
         const bool top = sc > a1;  // selects, not branches: the update runs on every lane
-        a2 = top ? a1 : fmaxf(a2, sc);
-        a1 = top ? sc : a1;
         v1 = top ? v : v1;
         lp1 = top ? l : lp1;
         u1 = top ? u : u1;
+        a2 = __builtin_amdgcn_fmed3f(a1, a2, sc);  // a1 >= a2: the second of the three
+        a1 = fmaxf(a1, sc);
       };
       if (whole) {
 #pragma unroll
@@ -220,12 +222,14 @@ __global__ __launch_bounds__(256) void finalize_kernel(const SamplePart* part, i
 
 hipError_t head_sample(const GemmProblem& p, const EpiParams& e, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0) return hipSuccess;
-  // Large vocabularies: 128 x 128 tiles on 2 x 2 waves (64 x 64 per wave, a third less
-  // LDS traffic per product), two blocks per CU; 26B-class head (V = 262144): 507 -> 407
-  // ms per generation against the tiles below.  Smaller ones: 128 x 64 tiles on 4 x 1
-  // waves, three blocks per CU (48 KB of LDS each), so that a block's VALU-heavy
-  // epilogue overlaps the others' MFMA main loops (1 % ahead on V = 32768).
-  if (p.N >= 40000) return launch_bf16<128, 128, 2, 2, 2, 2, EPI_SAMPLE>(p, e, s);
+  // Large vocabularies: 256 x 128 tiles, two blocks per CU (gemm_tall.h); against 128 x 128 tiles
+  // at two blocks per CU: 16 384 x 50 304 x 2 048 4 231 -> 3 762 us, 512 x 262 144 x 4 608 1 420 ->
+  // 1 180, 640 x 128 256 x 2 048 478 -> 455; 128 rows of 262 144 are 1 % slower, 40 to 240 rows of
+  // 128 256 1 to 4 % faster.  Smaller ones: 128 x 64 tiles on 4 x 1 waves, three blocks per CU
+  // (48 KB of LDS each), so that a block's VALU-heavy epilogue overlaps the others' MFMA main
+  // loops (V = 32 768, K = 768: whole step 175 against 181 us at 128 rows, 246 against 256 at
+  // 384, even at 1 024).
+  if (p.N >= 40000) return launch_tall<EPI_SAMPLE>(p, e, s);
   return launch_bf16<128, 64, 2, 4, 1, 3, EPI_SAMPLE>(p, e, s);
 }
 

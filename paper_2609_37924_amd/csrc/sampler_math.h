@@ -17,6 +17,11 @@ constexpr int SAMPLE_GROUP = 64;  // vocabulary entries per normaliser group
 
 __device__ __forceinline__ float bits_f(uint32_t b) { return __uint_as_float(b); }
 
+// a ^ b ^ c in one instruction
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
@@ -26,7 +31,7 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
     }
     // one 32x32->64 multiply per product (v_mad_u64_u32) gives both halves
     const uint64_t p0 = (uint64_t)0xD2511F53u * c[0], p1 = (uint64_t)0xCD9E8D57u * c[2];
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c[1] ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c[3] ^ k1;
+    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c[1], k0), n2 = xor3((uint32_t)(p0 >> 32), c[3], k1);
     c[0] = n0;
     c[1] = (uint32_t)p1;
     c[2] = n2;
@@ -37,7 +42,8 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
 // (2 (x >> 9) + 1) 2^-24: the float 1 + (x >> 9) 2^-23 minus 1 - 2^-24, a subtraction
 // that is exact (Sterbenz: the operands are within a factor of two)
 __device__ __forceinline__ float uniform01(uint32_t x) {
-  return __uint_as_float((x >> 9) | 0x3F800000u) - bits_f(0x3F7FFFFFu);
+  // (x >> 9) | 0x3F800000 as one funnel shift of (0x7F, x)
+  return __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, x, 9)) - bits_f(0x3F7FFFFFu);
 }
 
 // log(x) for positive normal x (within 1 ulp): x = 2^e m, m in [sqrt(1/2), sqrt(2)),
@@ -116,6 +122,10 @@ __device__ __forceinline__ float own_exp_sel_2p40(float y) {
   return under ? 0.0f : e;
 }
 
+// rint(own_exp(y) 2^40) with y < -30 taken at -30, where it is 0 too (e^-30 2^40 = 0.103): the
+// contract's fixed-point term without a select.
+__device__ __forceinline__ float own_exp_term(float y) { return rintf(own_exp_core(fmaxf(y, -30.0f), 40)); }
+
 struct Best {
   float score;
   int v;
@@ -142,10 +152,9 @@ struct Top2 {
   float a1 = -INFINITY, a2 = -INFINITY;
   int v1 = 0x7FFFFFFF;
   __device__ __forceinline__ void add(float a, int v) {  // by selects: no divergent branches
-    const bool t = a > a1;
-    a2 = t ? a1 : fmaxf(a2, a);
-    v1 = t ? v : v1;
-    a1 = t ? a : a1;
+    v1 = a > a1 ? v : v1;
+    a2 = __builtin_amdgcn_fmed3f(a1, a2, a);  // a1 >= a2: the second of the three
+    a1 = fmaxf(a1, a);
   }
 };
 

@@ -141,10 +141,7 @@ __global__ __launch_bounds__(256) void entropy_kernel(const float* logits, int V
         Bd += ex > 0.f ? (double)rintf(((-y) * ex) * TWO40) : 0.0;
         // the running top two, by selects
         const float sc = screen_score(lp, uniform01(c[e]));
-        const bool t1 = sc > top.a1;
-        top.a2 = t1 ? top.a1 : fmaxf(top.a2, sc);
-        top.v1 = t1 ? v : top.v1;
-        top.a1 = t1 ? sc : top.a1;
+        top.add(sc, v);
       }
       if (P) {
         PT* dst = P + (size_t)row * ldp + 4 * q;

@@ -63,13 +63,15 @@ def _head_product(tadm, cfg, dev, tensors, m, d, vocab, B, G):
         tadm.tadm_model_destroy(m)
 
 
-@pytest.mark.parametrize("vocab,B,G,masked", [(32768, 4, 256, 3), (40960, 4, 256, 129), (40964, 5, 250, 250),
-                                              (65536, 2, 700, 0)])
-def test_masked_only_head_with_few_rows(vocab, B, G, masked):
+@pytest.mark.parametrize("d,vocab,B,G,masked", [
+    (192, 32768, 4, 256, 3), (192, 40960, 4, 256, 129), (192, 40964, 5, 250, 250), (192, 65536, 2, 700, 0),
+    (64, 40960, 1, 256, 256), (128, 41000, 3, 86, 86), (256, 40960, 1, 300, 1), (320, 40100, 2, 260, 65),
+    (448, 65540, 1, 129, 129)])
+def test_masked_only_head_with_few_rows(d, vocab, B, G, masked):
     """The masked-only head, whose row count is known on the device alone, against the sampler
     on the logits of every row: the same tokens and confidences at any share of masked rows
     (the first `masked` positions of each row; a row bound of all positions)."""
-    tadm, cfg, dev, tensors, m = _model(192, vocab, B, 1, G)
+    tadm, cfg, dev, tensors, m = _model(d, vocab, B, 1, G)
     try:
         L = G + 1
         z = torch.randint(0, vocab, (B, L), dtype=torch.int32)
