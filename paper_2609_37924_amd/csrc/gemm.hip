@@ -460,15 +460,17 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmProblem p, EpiP
 }
 
 // Grids that leave CUs short of blocks: 64 x 64 tiles on the deep ring, three blocks per CU;
-// with at most 64 such tiles 32 x 32 ones, four times the blocks (64 x 3 072 x 2 048: 12.2 ->
-// 9.1 us; 64 x 16 384 x 2 048 has 256 tiles: 18.4 against 25.6).  Epilogues that pair weight
-// blocks keep 64 columns.
+// with at most 96 such tiles 32 x 32 ones, four times the blocks (64 x 3 072 x 2 048, 48 tiles:
+// 12.2 -> 9.1 us; 384 x 768 x 2 048, 72 tiles: 12.1 -> 10.3; with 192 tiles, 1 024 x 768 x 512, 5.6
+// against 7.3).  Epilogues that pair weight blocks keep 64 columns.  Splitting K of the unsplit
+// residual products over blocks would be faster still (384 x 768 x 2 048 in four: 6.8 us), but
+// the sums' other order moves tokens that nearly tie.
 template <EpiKind K>
 hipError_t launch_small(const GemmProblem& p, const EpiParams& e, hipStream_t s) {
   using E = Epi<K, bf16>;
   if constexpr (!E::kGlu && !TileEpi<E>::value && !RowEpi<E>::value) {
     const long t64 = (long)((p.M + 63) / 64) * ((p.N + 63) / 64);
-    if (t64 * p.ksplit <= 64) return launch_ring<32, 32, 8, 2, K>(p, e, s);
+    if (t64 <= 96) return launch_ring<32, 32, 8, 2, K>(p, e, s);
   }
   return launch_ring<64, 64, 3, 3, K>(p, e, s);
 }
@@ -631,73 +633,6 @@ __global__ __launch_bounds__(256) void resid_reduce_rms_kernel(const float* part
   }
 }
 
-// The second fusion product's rows from its K slices: x = h + g * (sum_s part[s, m, :] + b_2)
-// (s ascending), then x = LayerNorm(x) to resid and, with norm_g, y = bf16(RMSNorm(x)) for the
-// first denoiser layer: EPI_FUSION2 and the two norms in one pass.  One block of 256 threads
-// per row, as above.
-template <int NV>
-__global__ __launch_bounds__(256) void fusion_reduce_kernel(const float* part, int S, int M, int N, EpiParams e) {
-  __shared__ float red[4];
-  const int m = blockIdx.x, t = threadIdx.x;
-  const size_t MN = (size_t)M * N;
-  float4 x[NV];
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int c = (t + 256 * i) * 4;
-    x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (c < N) {
-      float4 acc = *reinterpret_cast<const float4*>(part + (size_t)m * N + c);
-#pragma unroll 4
-      for (int k = 1; k < S; ++k) {
-        const float4 v = *reinterpret_cast<const float4*>(part + k * MN + (size_t)m * N + c);
-        acc.x += v.x;
-        acc.y += v.y;
-        acc.z += v.z;
-        acc.w += v.w;
-      }
-      const float4 b = *reinterpret_cast<const float4*>(e.bias + c);
-      const float4 h = *reinterpret_cast<const float4*>(e.aux + (size_t)m * e.ld_aux + c);
-      const float4 g = *reinterpret_cast<const float4*>(e.gate + (size_t)m * e.ldg + c);
-      x[i] = make_float4(h.x + g.x * (acc.x + b.x), h.y + g.y * (acc.y + b.y), h.z + g.z * (acc.z + b.z),
-                         h.w + g.w * (acc.w + b.w));
-      s += x[i].x + x[i].y + x[i].z + x[i].w;
-    }
-  }
-  const float mu = block_sum(s, red) / N;
-  float ss = 0.f;
-#pragma unroll
-  for (int i = 0; i < NV; ++i)
-    if ((t + 256 * i) * 4 < N) {
-      const float a = x[i].x - mu, b = x[i].y - mu, c = x[i].z - mu, d = x[i].w - mu;
-      ss += a * a + b * b + c * c + d * d;
-    }
-  const float rs = rsqrtf(block_sum(ss, red) / N + e.ln_eps);
-  float sq = 0.f;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int c = (t + 256 * i) * 4;
-    if (c < N) {
-      const float4 w = *reinterpret_cast<const float4*>(e.ln_w + c), b = *reinterpret_cast<const float4*>(e.ln_b + c);
-      x[i] = make_float4((x[i].x - mu) * rs * w.x + b.x, (x[i].y - mu) * rs * w.y + b.y,
-                         (x[i].z - mu) * rs * w.z + b.z, (x[i].w - mu) * rs * w.w + b.w);
-      *reinterpret_cast<float4*>(e.resid + (size_t)m * e.ldr + c) = x[i];
-      sq += x[i].x * x[i].x + x[i].y * x[i].y + x[i].z * x[i].z + x[i].w * x[i].w;
-    }
-  }
-  if (!e.norm_g) return;  // the same for every thread
-  const float rr = rsqrtf(block_sum(sq, red) / N + e.norm_eps);
-  bf16* yr = static_cast<bf16*>(e.norm_out) + (size_t)m * N;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int c = (t + 256 * i) * 4;
-    if (c < N) {
-      const float4 g = *reinterpret_cast<const float4*>(e.norm_g + c);
-      store4(yr + c, x[i].x * rr * g.x, x[i].y * rr * g.y, x[i].z * rr * g.z, x[i].w * rr * g.w);
-    }
-  }
-}
-
 // K slices of a residual product on 256 x 256 tiles, one block per CU: the S in
 // [2, 16] (each slice >= 8 K tiles, slices as even as the tile count allows) that
 // minimises the modelled time, in K-step units: rounds of 256 blocks x (K tiles per
@@ -725,47 +660,37 @@ int resid_slices256(int M, int N, int K) {
   return best;
 }
 
-// The K slices of a product with few output tiles (a residual product, or the second fusion
-// product: N = d_model) and the tiles they run on.  The slices' products go to part [S, M, N]
-// and an ordered sum finishes the rows; each line below is the whole time with that sum and
-// the norm, weights from HBM, against the best of the others (an unsplit ring among them):
-//   up to 160 tiles of 64 x 64: on those, for 320 blocks (512 from 64 K tiles on), slices of at
-//     least three K tiles: 128 x 2 048 x 2 048 11.4 (unsplit 15.8), 128 x 2 048 x 8 192 19.5
-//     (49.5), 256 x 2 048 x 8 192 26.4 (50.0), 768 x 768 x 2 048 13.6 us (16.9)
-//   up to 320, and fewer than 64 K tiles: in two, 512 x 2 048 x 2 048 16.5 (20.4), 1 536 x 768 x
-//     2 048, 288 tiles, 18.3 (20.4)
-//   fewer than 64 tiles of 256 x 256 and up to 256 of 128 x 128: on those, for 512 blocks, slices
-//     of at least ten K tiles: 1 024 x 2 048 x 8 192 51.2 (256 x 256 in eight 55.0, unsplit 73.1),
-//     512 x 2 048 x 8 192 34.1 (40.6), 3 072 x 768 x 2 048 26.3 (28.7), 3 072 x 768 x 3 072 30.6
-//     (36.0); 1 024 x 2 048 x 2 048 stays whole: 21.9 against 25.4 in four
-//   otherwise on 256 x 256 tiles where resid_slices256 finds slices that win.
-enum SliceTiles { SLICE_NONE, SLICE_64, SLICE_128, SLICE_256 };
-SliceTiles slice_plan(int M, int N, int K, int* S) {
-  const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64), t128 = (long)((M + 127) / 128) * ((N + 127) / 128),
-             t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
+// K slices of a residual product with a long K and fewer than two 128 x 128 tiles per
+// CU (512 resident blocks): the S in {2, 4, 8} (each slice >= 16 K tiles) whose grid
+// best fills whole rounds of 512 blocks, the smaller S on ties
+int resid_slices(int M, int N, int K) {
+  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
   const int nk = K / 64;
-  *S = 1;
-  if (N % 4) return SLICE_NONE;
-  if (t64 <= 160) {
-    const long blocks = nk >= 64 ? GEMM_SMALL_PART / 4096 : 320;
-    *S = (int)std::min<long>(std::min<long>(nk / 3, blocks / t64), 10);
-    if (*S >= 2) return SLICE_64;
-    *S = 1;
-    return SLICE_NONE;
-  }
-  if (t64 <= 320 && nk >= 16 && nk < 64) {
-    *S = 2;
-    return SLICE_64;
-  }
-  if (t256 < 64 && t128 <= 256 && nk < 256) {
-    const int n = (int)std::min<long>(512 / t128, 8);
-    if (n >= 2 && nk / n >= 10) {
-      *S = n;
-      return SLICE_128;
+  if (tiles >= 512 || nk < 64 || N % 4) return 1;
+  int best = 1;
+  double best_fill = 0.0;
+  for (int S = 2; S <= 8; S *= 2) {
+    if (nk % S || nk / S < 16) break;
+    const long blocks = tiles * S, rounds = (blocks + 511) / 512;
+    const double fill = (double)blocks / (512.0 * rounds);
+    if (fill > best_fill + 1e-9) {
+      best = S;
+      best_fill = fill;
     }
   }
-  *S = resid_slices256(M, N, K);
-  return *S > 1 ? SLICE_256 : SLICE_NONE;
+  return best;
+}
+
+// The tiles a residual product's K slices run on.  Their number is given by the two rules
+// above whatever the tiles, so the sums have one order per shape; the tiles are the smallest
+// ones that still fit the chip at once: 64 x 64 (64 x 2 048 x 8 192, nine slices: 25 us on 256 x
+// 256 tiles -> 11; 128 rows 31.8 -> 19.5 with the sum), 128 x 128 (256 rows 37.7 -> 27.2), else
+// 256 x 256 (1 024 rows, eight slices: 55.0 against 64.3 and 83.9).
+enum SliceTiles { SLICE_64, SLICE_128, SLICE_256 };
+SliceTiles slice_tiles(int M, int N, int S, bool on256) {
+  const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64), t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
+  if (t64 * S <= 640) return SLICE_64;
+  return !on256 || t128 * S <= 512 ? SLICE_128 : SLICE_256;
 }
 
 // The slices' products of q (ksplit set) to f.out [S, M, N].
@@ -781,9 +706,8 @@ hipError_t launch_slices(SliceTiles t, const GemmProblem& q, const EpiParams& f,
 
 int gemm_split_slices(int M, int N, int K) { return split_slices(M, N, K); }
 int gemm_resid_slices(int M, int N, int K) {
-  int S;
-  slice_plan(M, N, K, &S);
-  return S;
+  const int S256 = resid_slices256(M, N, K);
+  return S256 > 1 ? S256 : resid_slices(M, N, K);
 }
 bool gemm_resid_norms(int M, int N, int K) { return gemm_resid_slices(M, N, K) > 1 && N % 4 == 0 && N <= 8192; }
 
@@ -794,8 +718,8 @@ hipError_t gemm(DType dt, const GemmProblem& p, EpiKind kind, const EpiParams& e
     if (splitk_scale(p, e, s, &err)) return err;
   }
   if (kind == EPI_RESID && dt == BF16 && e.part && !p.M_dev && p.K1 == p.K) {
-    int S;
-    const SliceTiles tiles = slice_plan(p.M, p.N, p.K, &S);
+    const int S256 = resid_slices256(p.M, p.N, p.K);
+    const int S = S256 > 1 ? S256 : resid_slices(p.M, p.N, p.K);
     if (S > 1) {  // the slices' products to part [S, M, N], then an ordered sum into resid
       GemmProblem q = p;
       q.ksplit = S;
@@ -803,7 +727,7 @@ hipError_t gemm(DType dt, const GemmProblem& p, EpiKind kind, const EpiParams& e
       f.out = e.part;
       f.ldo = p.N;
       f.split_stride = (size_t)p.M * p.N;
-      hipError_t err = launch_slices(tiles, q, f, s);
+      hipError_t err = launch_slices(slice_tiles(p.M, p.N, S, S256 > 1), q, f, s);
       if (err != hipSuccess) return err;
       if (e.norm_out) {  // the ordered sum and the RMSNorm of the updated rows in one pass
         if (!gemm_resid_norms(p.M, p.N, p.K) || !e.norm_g) return hipErrorInvalidValue;
@@ -829,25 +753,6 @@ hipError_t gemm(DType dt, const GemmProblem& p, EpiKind kind, const EpiParams& e
                          static_cast<const float*>(e.part), S, p.M, p.N, e.resid, e.ldr);
       return hipGetLastError();
     }
-  }
-  if (kind == EPI_FUSION2 && dt == BF16 && e.part && e.ln_w) {  // sliced, as gemm_resid_norms(M, N, K) says
-    int S;
-    const SliceTiles tiles = slice_plan(p.M, p.N, p.K, &S);
-    if (S < 2 || p.N > 8192 || p.M_dev || p.K1 != p.K) return hipErrorInvalidValue;
-    GemmProblem q = p;
-    q.ksplit = S;
-    EpiParams f;
-    f.out = e.part;
-    f.ldo = p.N;
-    f.split_stride = (size_t)p.M * p.N;
-    const hipError_t err = launch_slices(tiles, q, f, s);
-    if (err != hipSuccess) return err;
-    auto go = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(p.M), dim3(256), 0, s, static_cast<const float*>(e.part), S, p.M, p.N, e);
-      return hipGetLastError();
-    };
-    const int nv = (p.N + 1023) / 1024;
-    return nv <= 1 ? go(fusion_reduce_kernel<1>) : nv <= 2 ? go(fusion_reduce_kernel<2>) : nv <= 5 ? go(fusion_reduce_kernel<5>) : go(fusion_reduce_kernel<8>);
   }
   switch (kind) {
     case EPI_STORE: return dispatch<EPI_STORE>(dt, p, e, s);

@@ -106,11 +106,6 @@ struct EpiParams {
   const float* norm_g = nullptr;
   float norm_eps = 0.f;
   void* norm_out = nullptr;
-  // EPI_FUSION2 with part and ln_w set, where gemm_resid_norms(M, N, K): split over K; the
-  // ordered sum also takes the LayerNorm of the rows (affine ln_w, ln_b) to resid and, with
-  // norm_g, the RMSNorm of that to norm_out
-  const float *ln_w = nullptr, *ln_b = nullptr;
-  float ln_eps = 0.f;
 };
 
 // Sampling partial of one (row, 64-entry vocabulary group): the group maximum m_g of
@@ -133,12 +128,9 @@ inline void fast_divider(uint32_t d, uint32_t& mul, int& shift) {
 // K slices the bf16 EPI_SCALE_F32 product uses (1: no split); its part buffer needs
 // slices * M * N floats.
 int gemm_split_slices(int M, int N, int K);
-// K slices of a bf16 EPI_RESID or EPI_FUSION2 product given a part buffer (1: no split; else
-// part holds slices * M * N floats): few output tiles.
+// K slices of a bf16 EPI_RESID product given a part buffer (1: no split; else
+// part holds slices * M * N floats): long K with few 128 x 128 tiles.
 int gemm_resid_slices(int M, int N, int K);
-// Floats that the part buffer of a product sliced on up to 160 tiles of 64 x 64 never exceeds (at most
-// 512 blocks): a part buffer of that size from the start grows only for larger products.
-constexpr size_t GEMM_SMALL_PART = 512 * 64 * 64;
 // Whether a bf16 EPI_RESID product of this shape (split over K) can also write the RMSNorm
 // of its updated rows (EpiParams::norm_out); otherwise the caller normalises them.
 bool gemm_resid_norms(int M, int N, int K);

@@ -453,7 +453,6 @@ static tadm_status ensure_workspace(tadm_model* m) {
   TRY(ws_alloc(m, (void**)&w.xhat, N * 4));
   TRY(ws_alloc(m, (void**)&w.hq, N * 8));
   TRY(ws_alloc(m, (void**)&w.rscale, N * 4));
-  if (m->dt == BF16) TRY(ensure_kpart(m, GEMM_SMALL_PART));
   w.n_tok = (int)N;
   w.n_canvas = (int)N;
   return TADM_OK;
@@ -836,25 +835,9 @@ static tadm_status fusion(tadm_model* m, int B, int L, const float* c, const tad
     e.ld_aux = d;
     e.gate = s.fus_g;
     e.ldg = d;
-    if (m->dt == BF16 && gemm_resid_norms(N, d, 4 * d)) {  // the slice sum takes the norms that follow
-      TRY(ensure_kpart(m, (size_t)gemm_resid_slices(N, d, 4 * d) * N * d));
-      e.part = s.kpart;
-      e.ln_w = m->Wf(Y.ln_o_w);
-      e.ln_b = m->Wf(Y.ln_o_b);
-      e.ln_eps = cf.ln_eps;
-      if (cf.n_denoise > 0) {
-        e.norm_g = m->Wf(Y.layers[cf.n_shared + cf.n_anchor].attn_norm);
-        e.norm_eps = cf.rms_eps;
-        e.norm_out = s.xn;
-      }
-    }
-    TRY(prof_begin(m, TADM_STAGE_FUSION2, e.part != nullptr));
+    TRY(prof_begin(m, TADM_STAGE_FUSION2));
     HIPCHK(gemm(m->dt, p, EPI_FUSION2, e, st));
     TRY(prof_end(m, TADM_STAGE_FUSION2));
-    if (e.part) {
-      *prenormed = cf.n_denoise > 0;
-      return TADM_OK;
-    }
   }
   if (cf.n_denoise > 0) {
     const float* g0 = m->Wf(Y.layers[cf.n_shared + cf.n_anchor].attn_norm);
