@@ -465,12 +465,19 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmProblem p, EpiP
 // against 7.3).  Epilogues that pair weight blocks keep 64 columns.  Splitting K of the unsplit
 // residual products over blocks would be faster still (384 x 768 x 2 048 in four: 6.8 us), but
 // the sums' other order moves tokens that nearly tie.
+// More than 512 tiles of 64 x 64 put three blocks on some CUs; where 64 x 96 ones are at most
+// 512, no CU has more than two, which load 320 rows per K step instead of 384, and a CU's
+// loads (about 16 bytes a clock) are what bounds these: 3 072 x 768 x 768 12.3 -> 11.5 us,
+// x 2 048 21.8 -> 20.1, x 3 072 29.9 -> 26.8.  Below that 64 x 64 stays (2 304 x 768 x 2 048: 16.4
+// against 19.5).
 template <EpiKind K>
 hipError_t launch_small(const GemmProblem& p, const EpiParams& e, hipStream_t s) {
   using E = Epi<K, bf16>;
   if constexpr (!E::kGlu && !TileEpi<E>::value && !RowEpi<E>::value) {
     const long t64 = (long)((p.M + 63) / 64) * ((p.N + 63) / 64);
     if (t64 <= 96) return launch_ring<32, 32, 8, 2, K>(p, e, s);
+    const long t96 = (long)((p.M + 63) / 64) * ((p.N + 95) / 96);
+    if (t64 > 512 && t96 <= 512) return launch_ring<64, 96, 4, 2, K>(p, e, s);
   }
   return launch_ring<64, 64, 3, 3, K>(p, e, s);
 }

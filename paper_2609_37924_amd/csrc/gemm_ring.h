@@ -45,6 +45,24 @@ __device__ __forceinline__ void read_tile(uint32_t a, uint32_t w, bf16x8 (&fa)[2
       : "v"(a), "v"(w), "v"(a ^ 64), "v"(w ^ 64)
       : "memory");
 }
+__device__ __forceinline__ void read_tile(uint32_t a, uint32_t w, bf16x8 (&fa)[2][2], bf16x8 (&fw)[2][3]) {
+  asm volatile(
+      "ds_read_b128 %0, %10\n\t"
+      "ds_read_b128 %1, %10 offset:2048\n\t"
+      "ds_read_b128 %4, %11\n\t"
+      "ds_read_b128 %5, %11 offset:2048\n\t"
+      "ds_read_b128 %6, %11 offset:4096\n\t"
+      "ds_read_b128 %2, %12\n\t"
+      "ds_read_b128 %3, %12 offset:2048\n\t"
+      "ds_read_b128 %7, %13\n\t"
+      "ds_read_b128 %8, %13 offset:2048\n\t"
+      "ds_read_b128 %9, %13 offset:4096\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(fa[0][0]), "=&v"(fa[0][1]), "=&v"(fa[1][0]), "=&v"(fa[1][1]), "=&v"(fw[0][0]), "=&v"(fw[0][1]),
+        "=&v"(fw[0][2]), "=&v"(fw[1][0]), "=&v"(fw[1][1]), "=&v"(fw[1][2])
+      : "v"(a), "v"(w), "v"(a ^ 64), "v"(w ^ 64)
+      : "memory");
+}
 
 template <int BM, int BN, int NS, int MINB, EpiKind KIND>
 __global__ __launch_bounds__(256, MINB) void gemm_ring_kernel(GemmProblem p, EpiParams ep) {
@@ -103,7 +121,7 @@ __global__ __launch_bounds__(256, MINB) void gemm_ring_kernel(GemmProblem p, Epi
   // epilogue operands first: the oldest vector-memory operations, which the counted waits
   // below only ever wait for
   constexpr int NPRE = PreCount<E>::value;
-  constexpr bool PRE = NPRE > 0 && TN * TM * NPRE <= 16;
+  constexpr bool PRE = NPRE > 0 && TN * TM * NPRE <= 18;
   float4 pre[PRE ? TN : 1][PRE ? TM : 1][PRE ? NPRE : 1];
   if constexpr (PRE) {
 #pragma unroll
