@@ -183,7 +183,8 @@ def source_digest(source):
     while it matches."""
     src = os.path.join(ROOT, "paper_2609_37924_amd", "csrc")
     h = hashlib.sha256()
-    for f in ("common.h", "kernels.h", "gemm_kernel.h", "sampler_math.h", source):
+    for f in ("common.h", "kernels.h", "gemm_kernel.h", "gemm_pingpong.h", "gemm_ring.h", "gemm_tall.h",
+              "sampler_math.h", source):
         with open(os.path.join(src, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
