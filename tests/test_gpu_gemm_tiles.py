@@ -99,7 +99,7 @@ def test_masked_only_head_with_few_rows(d, vocab, B, G, masked):
 
 @pytest.mark.parametrize("d,F,B,L", [(128, 192, 1, 1), (128, 1024, 1, 64), (256, 512, 1, 65), (768, 2048, 1, 385),
                                      (128, 8192, 1, 61), (1024, 8192, 1, 128), (1024, 8192, 2, 300),
-                                     (1024, 2048, 2, 1037)])
+                                     (1024, 2048, 2, 1037), (768, 512, 1, 1001)])
 def test_residual_products(d, F, B, L):
     """Layers whose residual products are whole on 32, 64 and 96-column tiles, or split over K on
     64, 128 and 256-column tiles with the slice sum writing the following norm, against the
