@@ -125,6 +125,15 @@ __device__ __forceinline__ void mfma_acc(f32x4& acc, const bf16x8& w, const bf16
 __device__ __forceinline__ void mfma_first(f32x4& acc, const bf16x8& w, const bf16x8& a) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(w), "v"(a));
 }
+// A zero operand for mfma_first, where the accumulators are cleared before any fragment is
+// read.  Its registers are written by VALU instructions, and an MFMA that reads such a
+// register needs two wait states after the write; the compiler cannot see the MFMAs in the
+// assembly above, so the wait stands here (s_nop 1), ordered between the writes and them.
+__device__ __forceinline__ bf16x8 mfma_zero_operand() {
+  bf16x8 zero = {};
+  asm volatile("s_nop 1" : "+v"(zero));
+  return zero;
+}
 
 // Store of two neighbouring 16-feature blocks of 16 rows: lane holds features n0 + 4 (lane
 // >> 4) + [0, 4) of both blocks (x: the first, y: the second) for its row.  Swapping the

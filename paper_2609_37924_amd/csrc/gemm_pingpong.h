@@ -242,8 +242,7 @@ __global__ __launch_bounds__(512, 1) void gemm_pp_kernel(GemmProblem p, EpiParam
   while (more) {
     // zero accumulators, written by the matrix unit: they are accumulator registers from
     // their first value on
-    bf16x8 zero = {};
-    asm volatile("" : "+v"(zero));
+    const bf16x8 zero = mfma_zero_operand();
 #pragma unroll
     for (int a = 0; a < TN; ++a)
 #pragma unroll

@@ -138,8 +138,7 @@ __global__ __launch_bounds__(256, MINB) void gemm_ring_kernel(GemmProblem p, Epi
     if (s < nk) issue(s, s);
 
   f32x4 acc[TN][TM];
-  bf16x8 zero = {};
-  asm volatile("" : "+v"(zero));
+  const bf16x8 zero = mfma_zero_operand();
 #pragma unroll
   for (int a = 0; a < TN; ++a)
 #pragma unroll

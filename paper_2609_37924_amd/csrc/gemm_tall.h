@@ -128,8 +128,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tall_kernel(GemmProblem p, EpiPar
     issue_w(1, 1);
   }
   f32x4 acc[TN][TM];
-  bf16x8 zero = {};
-  asm volatile("" : "+v"(zero));
+  const bf16x8 zero = mfma_zero_operand();
 #pragma unroll
   for (int a = 0; a < TN; ++a)
 #pragma unroll
