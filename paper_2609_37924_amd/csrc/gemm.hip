@@ -2,8 +2,8 @@
 //
 // bf16 operands run on the MFMA kernel template of gemm_kernel.h with the epilogues
 // below; the tile shape is picked per call from the number of blocks it yields.
-// float32 operands (small fp32 models) run on a register-blocked VALU kernel with
-// the same epilogues.
+// float32 operands (small fp32 models) run on the float32 matrix instructions with the
+// same epilogues.
 #include <algorithm>
 
 #include "gemm_kernel.h"
@@ -338,85 +338,31 @@ struct Epi<EPI_GLU_GELU, T> {
   }
 };
 
-// ------------------------------------------------------------ fp32 VALU kernel
-// Tile 64 (rows) x 64 (features), K step 16; each thread computes 4 x 4 outputs.
-template <EpiKind KIND>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmProblem p, EpiParams ep) {
-  using E = Epi<KIND, float>;
-  __shared__ float sA[16][64 + 4];
-  __shared__ float sW[16][64 + 4];
-  __shared__ float xch[64][64 + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int tiles_m = (p.M + 63) / 64;
-  const int m0 = (blockIdx.x % tiles_m) * 64, n0 = (blockIdx.x / tiles_m) * 64;
-  const float* A1 = static_cast<const float*>(p.A1);
-  const float* A2 = static_cast<const float*>(p.A2);
-  const float* W = static_cast<const float*>(p.W);
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < p.K; k0 += 16) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c = tid + 256 * i, r = c >> 4, kk = c & 15, k = k0 + kk;
-      float av = 0.f, wv = 0.f;
-      if (k < p.K) {
-        const int gr = min(m0 + r, p.M - 1), gn = min(n0 + r, p.N - 1);
-        av = k < p.K1 ? A1[(size_t)gr * p.lda1 + k] : A2[(size_t)gr * p.lda2 + (k - p.K1)];
-        wv = W[(size_t)gn * p.ldw + k];
-      }
-      sA[kk][r] = av;
-      sW[kk][r] = wv;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], w[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = sA[kk][ty * 4 + i]; w[i] = sW[kk][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * w[j];
-    }
-    __syncthreads();
-  }
-  const int n = n0 + tx * 4;
-  if constexpr (E::kGlu) {
-    // features of the up half (offset 16 inside each 32-row block) come from thread tx + 4
-    const bool up = ((tx * 4) & 31) >= 16;
-    if (up)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) xch[ty * 4 + i][tx * 4 + j] = acc[i][j];
-    __syncthreads();
-    if (!up && n < p.N)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        if (m >= p.M) continue;
-        const float* u = &xch[ty * 4 + i][tx * 4 + 16];
-        const int f = ((n >> 5) << 4) + (n & 15);
-        E::glu(ep, m, f, f32x4{acc[i][0], acc[i][1], acc[i][2], acc[i][3]}, f32x4{u[0], u[1], u[2], u[3]});
-      }
-  } else {
-    if (n >= p.N) return;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = m0 + ty * 4 + i;
-      if (m < p.M) E::apply(ep, m, n, f32x4{acc[i][0], acc[i][1], acc[i][2], acc[i][3]});
-    }
-  }
+// ------------------------------------------------------------ fp32 kernels
+// float32 products on v_mfma_f32_16x16x4_f32 (a float32 multiply-add chain).  The order of
+// every sum depends on K alone, so that a row has the same bits whatever the number of rows
+// beside it: K in chunks of 16 (f32_chunk), the chunks in four quarters (f32_quarter), each
+// quarter one chain from zero, the four sums added in order.  Two kernels share it: a quarter
+// per wave for products too small to fill the chip otherwise, else a quarter after the other.
+// The line lies where both take the same time, at 2 048 tiles of 16 x 16 (us, small against
+// large, K = 64 / 256 / 512: 1 024 tiles 3.6 : 5.6, 6.5 : 10.5, 10.8 : 18.1; 2 048 tiles 4.7 : 5.8,
+// 10.9 : 10.8, 18.1 : 18.4; 4 096 tiles 7.3 : 6.0, 18.6 : 11.9, 34.7 : 19.6).
+constexpr long kF32SmallTiles = 2048;
+
+// the first chunk of quarter q
+__device__ __forceinline__ int f32_quarter(int K, int q) { return q * ((K + 15) / 16) / 4; }
+// acc += a chunk's products: a lane holds four consecutive k of its activation row and of its
+// weight row, product s takes element s of every lane's four (the same k on both sides)
+__device__ __forceinline__ void f32_chunk(f32x4& acc, const float4& w, const float4& a) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, a.x, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, a.y, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, a.z, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, a.w, acc, 0, 0, 0);
 }
 
-constexpr long kF32SmallTiles = 4096;
-
-// float32 products too small to fill the chip with the kernel above (which walks K in steps of
-// 16, one memory latency each): 16 x 16 tiles, the block's four waves splitting K, on
-// v_mfma_f32_16x16x4_f32 (a float32 multiply-add chain).  A lane loads four consecutive k of
-// its row at once, so that a 16-deep step is one load per operand and four products (product
-// s takes element s of every lane's four: the same k on both sides), four steps in flight;
-// the partial tiles are added in wave order.  32 rows, d = 64, d_ffn = 256: 13.6 -> 4.6 us per residual product,
-// 21.0 -> 5.0 for the second fusion product.
+// One 16 x 16 tile per block, the four waves a quarter of K each, four chunks' loads in flight.
+// 32 rows, d = 64, d_ffn = 256, against 64 x 64 tiles that walk K in steps of 16, one memory
+// latency each: 13.6 -> 4.6 us per residual product, 21.0 -> 5.0 for the second fusion product.
 template <EpiKind KIND>
 __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmProblem p, EpiParams ep) {
   using E = Epi<KIND, float>;
@@ -430,10 +376,10 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmProblem p, EpiP
   const float* A1 = static_cast<const float*>(p.A1) + (size_t)gr * p.lda1;
   const float* A2 = static_cast<const float*>(p.A2) + (size_t)gr * p.lda2;
   const float* W = static_cast<const float*>(p.W) + (size_t)gn * p.ldw;
-  const int nc = (p.K + 15) / 16, c0 = wave * nc / 4, c1 = (wave + 1) * nc / 4;
+  const int c1 = f32_quarter(p.K, wave + 1);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   constexpr int U = 4;
-  for (int c = c0; c < c1; c += U) {
+  for (int c = f32_quarter(p.K, wave); c < c1; c += U) {
     float4 a[U], w[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {  // K and K1 are multiples of 4
@@ -443,12 +389,8 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmProblem p, EpiP
       w[u] = in ? *reinterpret_cast<const float4*>(W + k) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u].x, a[u].x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u].y, a[u].y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u].z, a[u].z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u].w, a[u].w, acc, 0, 0, 0);
-    }
+    for (int u = 0; u < U; ++u)
+      if (c + u < c1) f32_chunk(acc, w[u], a[u]);
   }
   if (wave) part[wave - 1][lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
   __syncthreads();
@@ -461,6 +403,95 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmProblem p, EpiP
   // lane holds C[m0 + fr][n0 + 4 fq + j]
   const int m = m0 + fr, n = n0 + 4 * fq;
   if (m < p.M && n < p.N) E::apply(ep, m, n, acc);
+}
+
+// 64 x 64 tiles, a 32 x 32 part per wave (2 x 2); two chunks per step through two LDS buffers,
+// the next step's loads in flight over the present one's products.  LDS rows of 36 floats: the
+// 16-byte reads of 16 rows fall on different banks.  Bound by the matrix cores at depth (float32
+// MFMA and VALU have the same peak): a head of 2 048 x 32 768 x 512 with its sampler, whose 64 x 64
+// tiles were on the VALU before, 1 296 -> 903 us; 2 048 x 256 x 256 with its fusion 173 -> 95.
+template <EpiKind KIND>
+__global__ __launch_bounds__(256) void gemm_f32_large_kernel(GemmProblem p, EpiParams ep) {
+  using E = Epi<KIND, float>;
+  constexpr int TM = 2, TN = 2, CH = 2, LD = 16 * CH + 4;
+  __shared__ __attribute__((aligned(16))) float sA[2][64 * LD], sW[2][64 * LD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, fr = lane & 15, fq = lane >> 4;
+  const int tiles_m = (p.M + 63) / 64;  // of the launch
+  const int m0 = (blockIdx.x % tiles_m) * 64, n0 = (blockIdx.x / tiles_m) * 64;
+  if (p.M_dev) p.M = min(*p.M_dev, p.M);
+  if (m0 >= p.M) return;
+  // this thread's part of a step: four k of one row of each operand, per chunk
+  const int lr = tid >> 2, lk = 4 * (tid & 3);
+  const int gr = min(m0 + lr, p.M - 1), gn = min(n0 + lr, p.N - 1);
+  const float* A1 = static_cast<const float*>(p.A1) + (size_t)gr * p.lda1;
+  const float* A2 = static_cast<const float*>(p.A2) + (size_t)gr * p.lda2;
+  const float* W = static_cast<const float*>(p.W) + (size_t)gn * p.ldw;
+  const int nc = (p.K + 15) / 16, steps = (nc + CH - 1) / CH;
+  float4 ra[CH], rw[CH];
+  auto load = [&](int st) {
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {  // K and K1 are multiples of 4
+      const int k = 16 * (CH * st + h) + lk;
+      ra[h] = rw[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (k < p.K) {
+        ra[h] = *reinterpret_cast<const float4*>(k < p.K1 ? A1 + k : A2 + (k - p.K1));
+        rw[h] = *reinterpret_cast<const float4*>(W + k);
+      }
+    }
+  };
+  auto stage = [&](int buf) {
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {
+      *reinterpret_cast<float4*>(&sA[buf][lr * LD + 16 * h + lk]) = ra[h];
+      *reinterpret_cast<float4*>(&sW[buf][lr * LD + 16 * h + lk]) = rw[h];
+    }
+  };
+  f32x4 acc[TN][TM] = {}, sum[TN][TM] = {};
+  int q = 0, end = f32_quarter(p.K, 1);  // the quarter of the next chunk, and where it ends
+  auto close = [&] {                     // quarter q is summed
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        sum[i][j] = q ? sum[i][j] + acc[i][j] : acc[i][j];
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    ++q;
+    end = f32_quarter(p.K, q + 1);
+  };
+  const int ao = ((wave & 1) * 32 + fr) * LD + 4 * fq, wo = ((wave >> 1) * 32 + fr) * LD + 4 * fq;
+  load(0);
+  stage(0);
+  __syncthreads();
+  for (int st = 0; st < steps; ++st) {
+    const int buf = st & 1;
+    if (st + 1 < steps) load(st + 1);
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {
+      const int c = CH * st + h;
+      if (c >= nc) break;
+      while (c == end) close();
+      float4 a[TM], w[TN];
+#pragma unroll
+      for (int j = 0; j < TM; ++j) a[j] = *reinterpret_cast<const float4*>(&sA[buf][ao + 16 * j * LD + 16 * h]);
+#pragma unroll
+      for (int i = 0; i < TN; ++i) w[i] = *reinterpret_cast<const float4*>(&sW[buf][wo + 16 * i * LD + 16 * h]);
+#pragma unroll
+      for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) f32_chunk(acc[i][j], w[i], a[j]);
+    }
+    if (st + 1 < steps) stage(buf ^ 1);  // last read before the barrier of the step before
+    __syncthreads();
+  }
+  while (q < 4) close();
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+      const int m = m0 + 32 * (wave & 1) + 16 * j + fr, n = n0 + 32 * (wave >> 1) + 16 * i + 4 * fq;
+      if (m < p.M && n < p.N) E::apply(ep, m, n, sum[i][j]);
+    }
 }
 
 // Grids that leave CUs short of blocks: 64 x 64 tiles on the deep ring, three blocks per CU;
@@ -489,19 +520,18 @@ hipError_t launch_small(const GemmProblem& p, const EpiParams& e, hipStream_t s)
 template <EpiKind K>
 hipError_t dispatch(DType dt, const GemmProblem& p, const EpiParams& e, hipStream_t s) {
   if (dt == F32) {
+    // the kernels load four k at a time; float32 models run their gated units unfused (glu_f32)
     if constexpr (!Epi<K, float>::kGlu) {
-      // 4 096 tiles of 16 x 16 are 256 of 64 x 64, one block of the larger kernel per CU (two
-      // layers of d = 256 over 512 rows, whose widest product has 4 096: 408 -> 178 us)
+      if (p.K % 4 || p.K1 % 4 || p.lda1 % 4 || p.lda2 % 4 || p.ldw % 4) return hipErrorInvalidValue;
       const long t16 = (long)((p.M + 15) / 16) * ((p.N + 15) / 16);
-      const bool whole4 = p.K % 4 == 0 && p.K1 % 4 == 0 && p.lda1 % 4 == 0 && p.lda2 % 4 == 0 && p.ldw % 4 == 0;
-      if (whole4 && t16 <= kF32SmallTiles) {
+      const int t64 = ((p.M + 63) / 64) * ((p.N + 63) / 64);
+      if (t16 <= kF32SmallTiles)
         launch_timed(gemm_f32_small_kernel<K>, dim3((unsigned)t16), dim3(256), 0, s, p, e);
-        return hipGetLastError();
-      }
+      else
+        launch_timed(gemm_f32_large_kernel<K>, dim3(t64), dim3(256), 0, s, p, e);
+      return hipGetLastError();
     }
-    const int tiles = ((p.M + 63) / 64) * ((p.N + 63) / 64);
-    launch_timed(gemm_f32_kernel<K>, dim3(tiles), dim3(256), 0, s, p, e);
-    return hipGetLastError();
+    return hipErrorInvalidValue;
   }
   // tile choice by how many blocks each shape yields (256 CUs): GEMMs with many rows
   // take 256 x 256 tiles on 8 waves (gemm_pingpong.h), mid-size ones 128 x 128 at two blocks per CU, and

@@ -34,11 +34,54 @@ def test_product_tiles(d, vocab, B, G):
 
 
 @pytest.mark.parametrize("d,vocab,B,G", [(4, 4, 1, 1), (20, 12, 1, 17), (36, 100, 2, 15), (64, 256, 1, 24),
-                                         (132, 1028, 1, 33), (260, 516, 3, 16), (64, 4096, 1, 257)])
+                                         (132, 1028, 1, 33), (260, 516, 3, 16), (64, 4096, 1, 257),
+                                         (132, 2052, 3, 100)])
 def test_float32_product_tiles(d, vocab, B, G):
     """float32 models: small products (16 x 16 tiles, K split over four waves, K not a multiple
-    of 16) and one beyond them."""
+    of 16) and two beyond them (64 x 64 tiles, up to 2 048 tiles of 16 x 16 on the former)."""
     _head_product(*_model(d, vocab, B, 1, G, base="tiny"), d, vocab, B, G)
+
+
+@pytest.mark.parametrize("d,F,vocab,B,L", [(64, 256, 4096, 32, 17), (132, 272, 1028, 130, 33), (256, 1024, 512, 40, 65)])
+def test_float32_rows_do_not_depend_on_the_batch(d, F, vocab, B, L):
+    """A float32 row has the same bits alone and in a batch whose products (layers, fusion, head)
+    are large enough for the other kernel: its anchor states, its logits, and the tokens and
+    confidences of a masked-only step, whose head has a row bound of the whole batch."""
+    import paper_2609_37924_amd as tadm
+    cfg = synth.get_config("tiny", d_model=d, vocab=vocab, n_heads=d // 4, n_kv_heads=d // 4, head_dim=4, d_ffn=F,
+                           n_anchor=1, n_denoise=1)
+    dev = torch.device("cuda:0")
+    m = tadm.load_model(cfg, [t.to(dev) for t in synth.make_weights(cfg, perturb=True)], max_batch=B, max_seq=L,
+                        stream=torch.cuda.current_stream().cuda_stream)
+    try:
+        z = torch.randint(0, vocab, (B, L), generator=torch.Generator().manual_seed(5), dtype=torch.int32)
+        z[:, 1::2] = vocab
+        z = z.to(dev)
+
+        def step(b, full):
+            cache = tadm.tadm_cache_create(m, b, L)
+            zb = z[:b].contiguous()
+            tadm.tadm_anchor_forward(m, None, zb, b, L, 1, 1, cache)
+            h = torch.empty(b, L, d, device=dev)
+            tadm.tadm_cache_read(cache, tadm.CACHE_H, h)
+            logits = torch.empty(b, L - 1, vocab, device=dev) if full else None
+            nxt = torch.empty_like(zb)
+            tadm.tadm_denoise_step(m, None, zb, b, L, 1, cache, tadm.step_args(1, 1, L // 4, 2, 11, 1.0), logits, nxt)
+            ch = torch.empty(b, L - 1, dtype=torch.int32, device=dev)
+            cf = torch.empty(b, L - 1, device=dev)
+            tadm.tadm_debug_read(m, tadm.TAP_CHOICE, ch)
+            tadm.tadm_debug_read(m, tadm.TAP_CONF, cf)
+            torch.cuda.synchronize()
+            tadm.tadm_cache_destroy(cache)
+            out = dict(h=h[0], choice=ch[0], conf=cf[0], next=nxt[0])
+            return dict(out, logits=logits[0]) if full else out
+
+        alone = step(1, True)
+        for full in (True, False):
+            for name, x in step(B, full).items():
+                assert torch.equal(x, alone[name]), (name, full)
+    finally:
+        tadm.tadm_model_destroy(m)
 
 
 def _head_product(tadm, cfg, dev, tensors, m, d, vocab, B, G):
@@ -71,6 +114,10 @@ def test_masked_only_head_with_few_rows(d, vocab, B, G, masked):
     """The masked-only head, whose row count is known on the device alone, against the sampler
     on the logits of every row: the same tokens and confidences at any share of masked rows
     (the first `masked` positions of each row; a row bound of all positions)."""
+    _masked_only_head(d, vocab, B, G, masked)
+
+
+def _masked_only_head(d, vocab, B, G, masked):
     tadm, cfg, dev, tensors, m = _model(d, vocab, B, 1, G)
     try:
         L = G + 1
