@@ -116,11 +116,11 @@ __global__ __launch_bounds__(256) void sample_kernel(const float* logits, const 
         mx = fmaxf(mx, lp[e]);
       }
       mx = row16_max(mx);
-      // integer terms of at most 2^40, 64 of them a group: exact in float64
+      // integer terms of at most 2^40, 64 of them a group: exact in float64 (a NaN entry adds
+      // nothing, as in the sampling epilogue)
       double sd = 0.0;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sd += (double)rintf(own_exp_sel_2p40(lp[e] - mx));
-      sd = sd == sd ? sd : 0.0;  // four entries with a NaN among them add nothing
+      for (int e = 0; e < 4; ++e) sd += (double)own_exp_term(lp[e] - mx);
       const long long sg = (long long)row16_sum(sd);
       if ((lane & 15) == 0 && g < ng) {
         s_S[g] = sg;

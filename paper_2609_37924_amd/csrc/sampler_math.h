@@ -113,17 +113,10 @@ __device__ __forceinline__ float own_exp_sel(float y) {
   return under ? 0.0f : e;
 }
 
-// own_exp_sel(y) * 2^40 with the power of two folded into the exponent: the same value,
-// since both scalings by powers of two are exact in the normal range own_exp reaches
-// (its results lie in [e^-30, e^0.35] or are 0).
-__device__ __forceinline__ float own_exp_sel_2p40(float y) {
-  const bool under = y < -30.0f;
-  const float e = own_exp_core(under ? -30.0f : y, 40);
-  return under ? 0.0f : e;
-}
-
-// rint(own_exp(y) 2^40) with y < -30 taken at -30, where it is 0 too (e^-30 2^40 = 0.103): the
-// contract's fixed-point term without a select.
+// rint(own_exp(y) 2^40), the contract's fixed-point term, without a select: the power of two is
+// folded into the exponent (both scalings are exact in the normal range own_exp reaches, [e^-30,
+// e^0.35]), and y < -30 is taken at -30, where the term is 0 too (e^-30 2^40 = 0.103).  So is a
+// NaN: such an entry adds nothing.
 __device__ __forceinline__ float own_exp_term(float y) { return rintf(own_exp_core(fmaxf(y, -30.0f), 40)); }
 
 struct Best {

@@ -14,13 +14,14 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-def _model(d, vocab, B, P, G, base="small"):
+def _model(d, vocab, B, P, G, base="small", nan_rows=()):
     import paper_2609_37924_amd as tadm
     heads = dict(n_heads=d // 64, n_kv_heads=d // 64, d_ffn=64) if base == "small" else dict(
         n_heads=d // 4, n_kv_heads=d // 4, head_dim=4, d_ffn=16)
     cfg = synth.get_config(base, d_model=d, vocab=vocab, n_anchor=0, n_denoise=0, **heads)
     dev = torch.device("cuda:0")
     tensors = [t.to(dev) for t in synth.make_weights(cfg, perturb=True)]
+    tensors[2][list(nan_rows)] = float("nan")  # w_out
     m = tadm.load_model(cfg, tensors, max_batch=B, max_seq=P + G, stream=torch.cuda.current_stream().cuda_stream)
     return tadm, cfg, dev, tensors, m
 
@@ -117,8 +118,15 @@ def test_masked_only_head_with_few_rows(d, vocab, B, G, masked):
     _masked_only_head(d, vocab, B, G, masked)
 
 
-def _masked_only_head(d, vocab, B, G, masked):
-    tadm, cfg, dev, tensors, m = _model(d, vocab, B, 1, G)
+@pytest.mark.parametrize("d,vocab,B,G,masked", [(128, 32768, 1, 40, 40), (64, 40960, 2, 70, 33)])
+def test_masked_only_head_with_nan_logits(d, vocab, B, G, masked):
+    """The same where some vocabulary entries have a NaN logit in every row (NaN weights): alone in
+    a normaliser group, several in one, next to each other and 16 apart."""
+    _masked_only_head(d, vocab, B, G, masked, nan_rows=[5, 640, 641, 656, 700, vocab - 1])
+
+
+def _masked_only_head(d, vocab, B, G, masked, nan_rows=()):
+    tadm, cfg, dev, tensors, m = _model(d, vocab, B, 1, G, nan_rows=nan_rows)
     try:
         L = G + 1
         z = torch.randint(0, vocab, (B, L), dtype=torch.int32)
