@@ -340,10 +340,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm_bf16_kernel(GemmPro
   };
   using Yes = std::true_type;
   using No = std::false_type;
-  // Up projections (GLU / GELU epilogues) with more weight rows than activation rows
-  // issue each K tile's loads in two parts (26B-class gate/up, 1 024 x 73 728 x 4 608:
-  // 2 634 -> 2 542 ms per generation); the other products, and up projections with more
-  // activation rows, measured faster issuing the whole tile at once.
+  // Up projections (GLU / GELU epilogues) with more weight rows than activation rows and a
+  // short K issue each K tile's loads in two parts (launch_bf16)
   constexpr bool kSplitIssue = KIND == EPI_GLU_SILU || KIND == EPI_GLU_GELU || KIND == EPI_GELU;
 
   // K tile 0 landed and published, K tile 1 in flight, the first half's fragments read
@@ -363,9 +361,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINB) void gemm_bf16_kernel(GemmPro
     // registers) and K tile kt + 1 has landed: the buffer can take K tile kt + 2
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
-    // K tile kt + 2 into the buffer just freed: all of it at once, or, for the up
-    // projections whose weight is the larger operand, its weight rows now and its
-    // activation rows after the first half of the products
+    // K tile kt + 2 into the buffer just freed: all of it at once, or its weight rows now
+    // and its activation rows after the first half of the products
     const bool more = kt + 2 < nk, split = kSplitIssue && p.w_first;
     if (more) {
       if (split) issue_w(kt + 2, buf);
@@ -458,7 +455,9 @@ hipError_t launch_bf16(const GemmProblem& p0, const EpiParams& e, hipStream_t s)
   if (MINB <= 2) xcd_patch(p.rm, p.rn, BM, BN, 32 * MINB, p.gm, p.gn);
   p.band = p.rm > 0 ? 0 : xcd_band(tiles_m, BM, BN, 32 * MINB);
   const int blocks = p.band > 0 ? (tiles_m * tiles_n + 7) / 8 * 8 : tiles_m * tiles_n;
-  p.w_first = p.N > p.M;
+  // us, split against whole issue, GLU: 3 072 x 4 096 x 768 21.4 : 22.3, 1 536 x 6 144 x 1 536 29.8 :
+  // 31.8; 1 024 x 12 288 x 2 048 71.3 : 67.7, 1 024 x 8 192 x 4 608 84.1 : 80.5
+  p.w_first = p.N > p.M && p.K < 2048;
   launch_timed(gemm_bf16_kernel<BM, BN, ST, WGM, WGN, MINB, K>, dim3(blocks, p.ksplit), dim3(64 * WGM * WGN), 0, s, p,
                e);
   return hipGetLastError();
