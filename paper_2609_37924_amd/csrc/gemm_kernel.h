@@ -139,18 +139,15 @@ __device__ __forceinline__ bf16x8 mfma_zero_operand() {
 // >> 4) + [0, 4) of both blocks (x: the first, y: the second) for its row.  Swapping the
 // odd 16-lane groups of x with the even ones of y leaves every lane 8 consecutive features,
 // lanes fr, fr + 16, fr + 32, fr + 48 covering the row's 32 features: one 16-byte store per
-// lane in 64-byte runs instead of two 8-byte stores in 32-byte runs.
+// lane in 64-byte runs instead of two 8-byte stores in 32-byte runs.  N is a multiple of 8 (the
+// outputs stored so are a later product's K columns, multiples of 64 in bf16).
 __device__ __forceinline__ void store_rows(bf16* row, int n0, int N, bool row_ok, bf16x4 x, bf16x4 y, int fq) {
   const uint2 xu = __builtin_bit_cast(uint2, x), yu = __builtin_bit_cast(uint2, y);
   const auto s0 = __builtin_amdgcn_permlane16_swap(xu.x, yu.x, false, false);
   const auto s1 = __builtin_amdgcn_permlane16_swap(xu.y, yu.y, false, false);
   const int n = n0 + 16 * (fq & 1) + 8 * (fq >> 1);
-  if (row_ok && n < N) {
-    if (n + 8 <= N)
-      *reinterpret_cast<uint4*>(row + n) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-    else  // N is a multiple of 4
-      *reinterpret_cast<uint2*>(row + n) = make_uint2(s0[0], s1[0]);
-  }
+  if (row_ok && n < N)
+    *reinterpret_cast<uint4*>(row + n) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
 }
 __device__ __forceinline__ bf16x4 to_bf16x4(f32x4 v) { return bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]}; }
 

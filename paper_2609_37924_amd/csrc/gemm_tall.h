@@ -87,9 +87,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tall_kernel(GemmProblem p, EpiPar
   auto rsrc = [](const void* base) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, -1, 0x00027000);
   };
-  const bf16* A1 = static_cast<const bf16*>(p.A1);
-  const bf16* A2 = p.A2 ? static_cast<const bf16*>(p.A2) - p.K1 : A1;
-  const auto ra1 = rsrc(A1 + (size_t)m0 * p.lda1), ra2 = rsrc(A2 + (size_t)m0 * (p.A2 ? p.lda2 : p.lda1));
+  const auto ra = rsrc(static_cast<const bf16*>(p.A1) + (size_t)m0 * p.lda1);
   const auto rw = rsrc(static_cast<const bf16*>(p.W) + (size_t)n0 * p.ldw);
   uint32_t offA[2][4], offW[2][2];
 #pragma unroll
@@ -105,12 +103,10 @@ __global__ __launch_bounds__(256, 2) void gemm_tall_kernel(GemmProblem p, EpiPar
                    16 * lchunk;
   }
   auto issue_a = [&](int kt, int slot, int h) {  // half h of K tile kt into activation slot
-    const int k0 = kt * 64;
-    const auto r = k0 >= p.K1 ? ra2 : ra1;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)(smem + slot * AH + (wave + 4 * j) * 1024), 16, offA[h][j],
-                                               k0 * 2, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr)(smem + slot * AH + (wave + 4 * j) * 1024), 16, offA[h][j],
+                                               kt * 128, 0, 0);
   };
   auto issue_w = [&](int kt, int h) {  // weight half h of K tile kt into its slot 2 (kt % 2) + h
 #pragma unroll
@@ -219,14 +215,15 @@ __global__ __launch_bounds__(256, 2) void gemm_tall_kernel(GemmProblem p, EpiPar
 #endif
 }
 
+// One activation operand.  The grid is walked in bands, also where the row count is known to the
+// host: the head's is not (tile_of).
 template <EpiKind K>
 hipError_t launch_tall(const GemmProblem& p0, const EpiParams& e, hipStream_t s) {
+  if (p0.K1 < p0.K) return hipErrorInvalidValue;
   GemmProblem p = p0;
   const int tiles_m = (p.M + 255) / 256, tiles_n = (p.N + 127) / 128;
-  if (!p.M_dev) xcd_regions(tiles_m, tiles_n, 256, 128, p.rm, p.rn);
-  xcd_patch(p.rm, p.rn, 256, 128, 64, p.gm, p.gn);
-  p.band = p.rm > 0 ? 0 : xcd_band(tiles_m, 256, 128, 64);
-  const int blocks = p.band > 0 ? (tiles_m * tiles_n + 7) / 8 * 8 : tiles_m * tiles_n;
+  p.band = xcd_band(tiles_m, 256, 128, 64);
+  const int blocks = (tiles_m * tiles_n + 7) / 8 * 8;
   launch_timed(gemm_tall_kernel<K>, dim3(blocks), dim3(256), 0, s, p, e);
   return hipGetLastError();
 }

@@ -400,17 +400,6 @@ static tadm_status ws_alloc(tadm_model* m, void** p, size_t bytes) {
   return TADM_OK;
 }
 
-// Workspace of K-slice products (grown on demand).
-static tadm_status ensure_kpart(tadm_model* m, size_t floats) {
-  Workspace& s = m->ws;
-  if (s.kpart_cap >= floats) return TADM_OK;
-  if (s.kpart) HIPCHK(hipFree(s.kpart));
-  s.kpart = nullptr;
-  HIPCHK(hipMalloc((void**)&s.kpart, floats * 4));
-  s.kpart_cap = floats;
-  return TADM_OK;
-}
-
 static tadm_status ensure_workspace(tadm_model* m) {
   Workspace& w = m->ws;
   if (w.n_tok) return TADM_OK;
@@ -465,6 +454,17 @@ static tadm_status ensure_logits(tadm_model* m, size_t n) {
   w.logits = nullptr;
   HIPCHK(hipMalloc((void**)&w.logits, n * 4));
   w.logits_cap = n;
+  return TADM_OK;
+}
+
+// Workspace of K-slice products (grown on demand).
+static tadm_status ensure_kpart(tadm_model* m, size_t floats) {
+  Workspace& s = m->ws;
+  if (s.kpart_cap >= floats) return TADM_OK;
+  if (s.kpart) HIPCHK(hipFree(s.kpart));
+  s.kpart = nullptr;
+  HIPCHK(hipMalloc((void**)&s.kpart, floats * 4));
+  s.kpart_cap = floats;
   return TADM_OK;
 }
 
