@@ -224,9 +224,9 @@ struct Epi<EPI_QKV_ROPE, T> {
                                   int nb, int lane, char* lds) {
     constexpr int WTN = TN * 16, WTM = NB * 16;
     const int fr = lane & 15, fq = lane >> 4;
-    // the staging maps rows and chunks to lanes by powers of two: 48-column strips (64 x 96
-    // tiles) are stored directly (block workload's 1 024 x 3 072 x 2 048, heads of 128: 33.0 us
-    // on 64 x 64 tiles staged, 27.4 on these)
+    // the staging maps rows and chunks to lanes by powers of two; the 48-column strips of 64 x
+    // 96 tiles are stored directly, which the tiles outweigh (1 024 x 3 072 x 2 048, heads of 128:
+    // 27.4 us so, 33.0 on staged 64 x 64 tiles)
     constexpr bool kStaged = (WTN & (WTN - 1)) == 0;
     if (!kStaged || e.dh % WTN != 0) {  // the same for every wave of the grid
 #pragma unroll
@@ -501,9 +501,11 @@ __global__ __launch_bounds__(256) void gemm_f32_large_kernel(GemmProblem p, EpiP
 // residual products over blocks would be faster still (384 x 768 x 2 048 in four: 6.8 us), but
 // the sums' other order moves tokens that nearly tie.
 // More than 512 tiles of 64 x 64 put three blocks on some CUs; where 64 x 96 ones are at most
-// 512, no CU has more than two, which load 320 rows per K step instead of 384, and a CU's
-// loads (about 16 bytes a clock) are what bounds these: 3 072 x 768 x 768 12.3 -> 11.5 us,
-// x 2 048 21.8 -> 20.1, x 3 072 29.9 -> 26.8.  Below that 64 x 64 stays (2 304 x 768 x 2 048: 16.4
+// 512, no CU has more than two, which load 320 rows per K step instead of 384 (3 072 x 768 x 768
+// 12.3 -> 11.5 us, x 2 048 21.8 -> 20.1, x 3 072 29.9 -> 26.8).  Over the range of the rule, 64 x 64
+// against 64 x 96: 2 880 x 1 024 x 4 096 49.8 : 36.8, 2 240 x 1 024 x 1 024 15.6 : 13.1, 640 x 4 608 x
+// 4 608 58.7 : 51.3, 1 024 x 3 072 x 1 024 15.0 : 14.5, 1 088 x 2 048 x 2 048 20.6 : 20.0, 704 x 3 072 x 512
+// 9.2 : 9.4, 576 x 4 096 x 1 024 12.7 : 13.8.  Below 513 tiles 64 x 64 stays (2 304 x 768 x 2 048: 16.4
 // against 19.5).
 template <EpiKind K>
 hipError_t launch_small(const GemmProblem& p, const EpiParams& e, hipStream_t s) {
@@ -674,7 +676,8 @@ __global__ __launch_bounds__(256) void resid_reduce_rms_kernel(const float* part
   }
 }
 
-// K slices of a residual product on 256 x 256 tiles, one block per CU: the S in
+// K slices of a residual product, counted as for 256 x 256 tiles at one block per CU whatever
+// tiles they run on (slice_tiles): the count is the order of the sums, which outputs keep.  The S in
 // [2, 16] (each slice >= 8 K tiles, slices as even as the tile count allows) that
 // minimises the modelled time, in K-step units: rounds of 256 blocks x (K tiles per
 // slice + 2 for a block's prologue and epilogue), plus 1.5 per slice for the ordered
@@ -723,10 +726,13 @@ int resid_slices(int M, int N, int K) {
 }
 
 // The tiles a residual product's K slices run on.  Their number is given by the two rules
-// above whatever the tiles, so the sums have one order per shape; the tiles are the smallest
-// ones that still fit the chip at once: 64 x 64 (64 x 2 048 x 8 192, nine slices: 25 us on 256 x
-// 256 tiles -> 11; 128 rows 31.8 -> 19.5 with the sum), 128 x 128 (256 rows 37.7 -> 27.2), else
-// 256 x 256 (1 024 rows, eight slices: 55.0 against 64.3 and 83.9).
+// above whatever the tiles, so the sums have one order per shape.  64 x 64 tiles while their
+// blocks fit the chip at once (512, two per CU) or nearly so (64 x 2 048 x 8 192, nine slices: 25 us
+// on 256 x 256 tiles -> 11).  us, 64 x 64 against 128 x 128 tiles, by the number of the former: 416
+// blocks 16.2 : 22.7 and 19.3 : 25.0, 512 10.2 : 14.4, 28.7 : 40.6 and 35.3 : 44.0; 576 17.9 : 18.8 and
+// 15.8 : 15.3, 624 21.0 : 22.8 and 22.8 : 24.9, 640 15.5 : 16.3 and 15.9 : 15.4; 832 28.4 : 26.7, 864 17.3 :
+// 16.4, 1 024 54.9 : 46.6.  Then 128 x 128 (256 rows 37.7 -> 27.2 against 256 x 256), else 256 x 256
+// (1 024 rows, eight slices: 55.0 against 64.3 and 83.9).
 enum SliceTiles { SLICE_64, SLICE_128, SLICE_256 };
 SliceTiles slice_tiles(int M, int N, int S, bool on256) {
   const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64), t128 = (long)((M + 127) / 128) * ((N + 127) / 128);

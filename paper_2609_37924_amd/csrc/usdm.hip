@@ -256,6 +256,7 @@ __global__ void init_uniform_kernel(int32_t* tok, int ld, int col0, int B, int n
   tok[(size_t)b * ld + col0 + t] = uniform_token(INIT_WORD0, (uint32_t)(pos_base + t), (uint32_t)b, block, k0, k1, V);
 }
 
+// ET[n, v] = E[v, n] for v < V, 0 for V <= v < ldt; 64 x 64 tiles through LDS
 template <class T>
 __global__ __launch_bounds__(256) void transpose_kernel(const T* E, int V, int d, T* ET, int ldt) {
   __shared__ T tile[64][65];
