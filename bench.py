@@ -32,7 +32,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
-PEAK_FP32_TFLOPS = 157.3    # MI355X fp32 vector (the float32 models' products and attention run on the VALU)
+PEAK_FP32_TFLOPS = 157.3    # MI355X fp32, vector and matrix alike (the float32 models' kernels)
 PEAK_HBM_GBS = 8000.0
 
 
@@ -128,19 +128,20 @@ def schedule_work(cfg, B, K):
 # Kernel groups: the stages that launch one kernel on these workloads (the attention
 # output and FFN down projections share the residual-epilogue GEMM), the bound, the
 # pattern of its rocprofv3 kernel name and the source it is built from.
+GEMM = r"gemm_(bf16|pp|ring|tall)_kernel<.*EpiKind"  # the bf16 product loops
 KERNELS = [
     ("residual-epilogue GEMM (attention output + FFN down projections, bf16 MFMA)", ("oproj", "ffn_down"),
-     "mfma", r"gemm_bf16_kernel<.*EpiKind\)2>", "gemm.hip"),
+     "mfma", GEMM + r"\)2>", "gemm.hip"),
     ("FFN gate/up GEMM with GLU epilogue (bf16 MFMA)", ("ffn_up",), "mfma",
-     r"gemm_bf16_kernel<.*EpiKind\)[345]>", "gemm.hip"),
-    ("q/k/v GEMM with rotary epilogue (bf16 MFMA)", ("qkv",), "mfma", r"gemm_bf16_kernel<.*EpiKind\)13>",
+     GEMM + r"\)[345]>", "gemm.hip"),
+    ("q/k/v GEMM with rotary epilogue (bf16 MFMA)", ("qkv",), "mfma", GEMM + r"\)13>",
      "gemm.hip"),
     ("attention (bf16 MFMA)", ("attn",), "mfma", r"attn_bf16_kernel", "attention.hip"),
     ("vocabulary projection with the sampling epilogue (bf16 MFMA + Gumbel-max/normaliser partials)", ("head",),
-     "mfma", r"gemm_bf16_kernel<.*EpiKind\)14>", "head_sample.hip"),
+     "mfma", GEMM + r"\)14>", "head_sample.hip"),
     ("fusion GEMM 1 (LN inputs -> hidden + gate, bf16 MFMA)", ("fusion1",), "mfma",
-     r"gemm_bf16_kernel<.*EpiKind\)6>", "gemm.hip"),
-    ("fusion GEMM 2 (gated residual, bf16 MFMA)", ("fusion2",), "mfma", r"gemm_bf16_kernel<.*EpiKind\)7>",
+     GEMM + r"\)6>", "gemm.hip"),
+    ("fusion GEMM 2 (gated residual, bf16 MFMA)", ("fusion2",), "mfma", GEMM + r"\)7>",
      "gemm.hip"),
     ("sampler finalize: merge of the group partials into token + confidence", ("sample",), "hbm",
      r"finalize_kernel", "head_sample.hip"),
@@ -149,7 +150,7 @@ KERNELS = [
 
 # The fp32 K-slice products of split residual products (the only fp32-output products
 # on the bf16 workloads' layer path; the kernel_bench programs run nothing else of that kind)
-SLICE_PATTERN = r"gemm_bf16_kernel<(256, 256|128, 128).*EpiKind\)1>"
+SLICE_PATTERN = GEMM + r"\)1>"
 
 
 def kernel_table(cfg, B, K, stages):
@@ -163,8 +164,8 @@ def kernel_table(cfg, B, K, stages):
         if not n or not w:
             continue
         expect = sum(launches[x] for x in names)
-        if bound == "mfma" and cfg["dtype"] != "bf16":  # float32 kernels: VALU arithmetic
-            desc, bound = desc.replace("bf16 MFMA", "fp32 VALU"), "alu"
+        if bound == "mfma" and cfg["dtype"] != "bf16":  # float32 kernels: one peak for MFMA and VALU
+            desc, bound = desc.replace("bf16 MFMA", "fp32 VALU" if "attn" in names else "fp32 MFMA"), "alu"
         peak, unit, scale = ((PEAK_BF16_TFLOPS if bound == "mfma" else PEAK_FP32_TFLOPS), "TFLOP/s", 1e12) \
             if bound != "hbm" else (PEAK_HBM_GBS, "GB/s", 1e9)
         achieved = w / (ms / 1e3) / scale

@@ -193,6 +193,8 @@ int main(int argc, char** argv) {
   uint16_t* wout = random_bf16((size_t)V * d, 1.0f / sqrtf((float)d), 10);
   int32_t* hidx = alloc<int32_t>((size_t)Mh);
   hipLaunchKernelGGL(fill_iota, dim3(64), dim3(256), 0, 0, hidx, Mh);
+  int* hcount = alloc<int>(1);  // the head's row count is on the device, as in a masked-only step
+  HIP_OK(hipMemcpy(hcount, &Mh, sizeof(int), hipMemcpyHostToDevice));
   SamplePart* hpart = alloc<SamplePart>((size_t)Mh * ng);
   int32_t* row_map = alloc<int32_t>((size_t)M);
   int32_t* canvas = alloc<int32_t>((size_t)M);
@@ -298,6 +300,7 @@ int main(int argc, char** argv) {
   });
   stage("head", 2.0 * Mh * d * V, [&]() {
     GemmProblem p{Mh, V, d, xn, d, d, nullptr, 0, wout, d};
+    p.M_dev = hcount;
     EpiParams e;
     e.rows_idx = hidx;
     e.Lc = L;
@@ -341,7 +344,7 @@ int main(int argc, char** argv) {
     if (p) HIP_OK(hipFree(p));
   for (void* p : {(void*)xn, (void*)wqkv, (void*)wo, (void*)wup, (void*)wdown, (void*)ao, (void*)ffn, (void*)q,
                   (void*)kc, (void*)vt, (void*)x, (void*)rope, (void*)part, (void*)copy_dst, (void*)gain,
-                  (void*)xn2, (void*)wout, (void*)hidx, (void*)hpart})
+                  (void*)xn2, (void*)wout, (void*)hidx, (void*)hcount, (void*)hpart})
     HIP_OK(hipFree(p));
   HIP_OK(hipStreamDestroy(st));
   return 0;

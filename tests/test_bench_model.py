@@ -104,7 +104,7 @@ def test_bench_prints_native_driver_arguments(root):
 @pytest.mark.parametrize("name", ["tiny"] + CONFIGS)
 def test_kernel_table_takes_counters_for_every_workload(name):
     """The per-kernel table and its counter fields build for every workload, the float32
-    one included (its rows are described as VALU kernels, so counters are looked up by
+    one included (its rows' descriptions differ, so counters are looked up by
     stage); a stored figure is attached only where the committed summary matches."""
     cfg = synth.get_config(name)
     K = cfg["Ks"][0]
