@@ -448,7 +448,7 @@ hipError_t launch_bf16(const GemmProblem& p0, const EpiParams& e, hipStream_t s)
   GemmProblem p = p0;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   if (!p.M_dev) xcd_regions(tiles_m, tiles_n, BM, BN, p.rm, p.rn);
-  // one block per CU for the 8-wave tiles, MINB per CU otherwise (LDS bounds both)
+  // MINB blocks per CU (LDS bounds them)
   if (MINB <= 2) xcd_patch(p.rm, p.rn, BM, BN, 32 * MINB, p.gm, p.gn);
   p.band = p.rm > 0 ? 0 : xcd_band(tiles_m, BM, BN, 32 * MINB);
   const int blocks = p.band > 0 ? (tiles_m * tiles_n + 7) / 8 * 8 : tiles_m * tiles_n;
