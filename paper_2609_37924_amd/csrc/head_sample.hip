@@ -222,14 +222,23 @@ __global__ __launch_bounds__(256) void finalize_kernel(const SamplePart* part, i
 
 hipError_t head_sample(const GemmProblem& p, const EpiParams& e, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0) return hipSuccess;
-  // Large vocabularies: 256 x 128 tiles, two blocks per CU (gemm_tall.h); against 128 x 128 tiles
-  // at two blocks per CU: 16 384 x 50 304 x 2 048 4 231 -> 3 762 us, 512 x 262 144 x 4 608 1 420 ->
-  // 1 180, 640 x 128 256 x 2 048 478 -> 455; 128 rows of 262 144 are 1 % slower, 40 to 240 rows of
-  // 128 256 1 to 4 % faster.  Smaller ones: 128 x 64 tiles on 4 x 1 waves, three blocks per CU
-  // (48 KB of LDS each), so that a block's VALU-heavy epilogue overlaps the others' MFMA main
-  // loops (V = 32 768, K = 768: whole step 175 against 181 us at 128 rows, 246 against 256 at
-  // 384, even at 1 024).
-  if (p.N >= 40000) return launch_tall<EPI_SAMPLE>(p, e, s);
+  // Smaller vocabularies: 128 x 64 tiles on 4 x 1 waves, three blocks per CU (48 KB of LDS each),
+  // so that a block's VALU-heavy epilogue overlaps the others' MFMA loops (V = 32 768, K = 768:
+  // whole step, 256 x 128 tiles against these, 175 : 181 us at 128 rows, 246 : 256 at 384, even at
+  // 1 024).  Large ones: 256 x 128 tiles (gemm_tall.h) or 128 x 128 ones, both at two blocks per
+  // CU, by their rounds of 512 blocks over the row bound: a round of the former takes 1.6 to 1.7
+  // times one of the latter.  us, 256 x 128 against 128 x 128 tiles; 262 144 x 4 608: 16 rows 451 :
+  // 414, 128 rows 517 : 501, 256 650 : 814, 272 1 079 : 1 039, 384 1 099 : 1 082, 512 1 196 : 1 402, 640
+  // 1 725 : 1 742, 1 024 2 284 : 2 735; 50 304 x 2 048: 128 52 : 50, 160 69 : 82, 288 142 : 105, 512 146 :
+  // 142, 640 179 : 160, 800 239 : 217, 1 024 246 : 251, 16 512 3 720 : 4 246; 128 256 x 2 048: 128 138 :
+  // 141, 256 178 : 208, 272 281 : 258, 640 403 : 450.  Where fewer rows than the bound are masked
+  // the choice may miss by as much (640 of 16 512 rows: 181 : 170).
+  if (p.N >= 40000) {
+    const long tn = (p.N + 127) / 128, rounds256 = (tn * ((p.M + 255) / 256) + 511) / 512,
+               rounds128 = (tn * ((p.M + 127) / 128) + 511) / 512;
+    return 5 * rounds256 <= 3 * rounds128 ? launch_tall<EPI_SAMPLE>(p, e, s)
+                                          : launch_bf16<128, 128, 2, 2, 2, 2, EPI_SAMPLE>(p, e, s);
+  }
   return launch_bf16<128, 64, 2, 4, 1, 3, EPI_SAMPLE>(p, e, s);
 }
 
