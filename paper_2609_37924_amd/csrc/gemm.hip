@@ -224,9 +224,8 @@ struct Epi<EPI_QKV_ROPE, T> {
                                   int nb, int lane, char* lds) {
     constexpr int WTN = TN * 16, WTM = NB * 16;
     const int fr = lane & 15, fq = lane >> 4;
-    // the staging maps rows and chunks to lanes by powers of two; the 48-column strips of 64 x
-    // 96 tiles are stored directly, which the tiles outweigh (1 024 x 3 072 x 2 048, heads of 128:
-    // 27.4 us so, 33.0 on staged 64 x 64 tiles)
+    // the staging maps rows and chunks to lanes by powers of two: the 48-column strips of 64 x
+    // 96 tiles are stored directly
     constexpr bool kStaged = (WTN & (WTN - 1)) == 0;
     if (!kStaged || e.dh % WTN != 0) {  // the same for every wave of the grid
 #pragma unroll
@@ -494,27 +493,39 @@ __global__ __launch_bounds__(256) void gemm_f32_large_kernel(GemmProblem p, EpiP
     }
 }
 
-// Grids that leave CUs short of blocks: 64 x 64 tiles on the deep ring, three blocks per CU;
-// with at most 96 such tiles 32 x 32 ones, four times the blocks (64 x 3 072 x 2 048, 48 tiles:
-// 12.2 -> 9.1 us; 384 x 768 x 2 048, 72 tiles: 12.1 -> 10.3; with 192 tiles, 1 024 x 768 x 512, 5.6
-// against 7.3).  Epilogues that pair weight blocks keep 64 columns.  Splitting K of the unsplit
-// residual products over blocks would be faster still (384 x 768 x 2 048 in four: 6.8 us), but
-// the sums' other order moves tokens that nearly tie.
-// More than 512 tiles of 64 x 64 put three blocks on some CUs; where 64 x 96 ones are at most
-// 512, no CU has more than two, which load 320 rows per K step instead of 384 (3 072 x 768 x 768
-// 12.3 -> 11.5 us, x 2 048 21.8 -> 20.1, x 3 072 29.9 -> 26.8).  Over the range of the rule, 64 x 64
-// against 64 x 96: 2 880 x 1 024 x 4 096 49.8 : 36.8, 2 240 x 1 024 x 1 024 15.6 : 13.1, 640 x 4 608 x
-// 4 608 58.7 : 51.3, 1 024 x 3 072 x 1 024 15.0 : 14.5, 1 088 x 2 048 x 2 048 20.6 : 20.0, 704 x 3 072 x 512
-// 9.2 : 9.4, 576 x 4 096 x 1 024 12.7 : 13.8.  Below 513 tiles 64 x 64 stays (2 304 x 768 x 2 048: 16.4
-// against 19.5).
+// Grids that leave CUs short of blocks.  Up to 512 tiles of 64 x 64, two per CU, run on the deep
+// ring (gemm_ring.h); with at most 96 such tiles 32 x 32 ones, four times the blocks (64 x 3 072 x
+// 2 048, 48 tiles: 12.2 -> 9.1 us; 384 x 768 x 2 048, 72 tiles: 12.1 -> 10.3; with 192 tiles, 1 024 x
+// 768 x 512, 5.6 against 7.3).  Epilogues that pair weight blocks keep 64 columns.  Splitting K of
+// the unsplit residual products over blocks would be faster still (384 x 768 x 2 048 in four: 6.8
+// us), but the sums' other order moves tokens that nearly tie.
+//
+// More than 512 put three blocks on some CUs, which hide each other's latency:
+//  - 64 x 96 tiles where they are at most 512 (residual, fusion 2 and float32 outputs, q/k/v of a
+//    long K, whose strips then leave LDS out): no CU has more than two, which load 320 rows per K step instead of 384.  us, 64 x 64 on the two-buffer
+//    loop against 64 x 96: 3 072 x 768 x 2 048 21.2 : 19.9, 3 500 x 768 x 3 072 30.5 : 28.9, 1 272 x
+//    2 048 x 2 048 21.3 : 20.3, 640 x 4 608 x 4 096 52.7 : 44.8, 2 625 x 1 024 x 1 024 14.5 : 13.5, 3 000 x
+//    768 x 768 11.8 : 11.9; q/k/v 1 024 x 2 304 x 768 10.7 : 11.8, 1 024 x 3 072 x 2 048 21.7 : 21.3 (a
+//    refresh step of three such layers 1 270 : 1 260).
+//  - else the two-buffer loop (gemm_kernel.h); us, it against the ring: 768 x 3 840 x 1 536 15.9 :
+//    17.5, 1 024 x 2 304 x 768 9.5 : 10.3, 300 x 10 240 x 4 096 55.2 : 61.4, fusion 1 900 x 3 840 x 1 536
+//    22.5 : 24.9, 1 800 x 2 048 x 8 192 110.8 : 143.2.  Up to 768 tiles the ring stays for the up
+//    projections (300 x 8 192 x 2 048 26.9 : 25.5, 768 x 3 072 x 768 10.6 : 10.2) and for at most 256
+//    rows, whose weights stream from memory (200 x 10 240 x 4 096 50.8 : 46.7).
 template <EpiKind K>
 hipError_t launch_small(const GemmProblem& p, const EpiParams& e, hipStream_t s) {
   using E = Epi<K, bf16>;
-  if constexpr (!E::kGlu && !TileEpi<E>::value && !RowEpi<E>::value) {
-    const long t64 = (long)((p.M + 63) / 64) * ((p.N + 63) / 64);
+  constexpr bool kFragments = !E::kGlu && !TileEpi<E>::value && !RowEpi<E>::value;
+  constexpr bool kUp = K == EPI_GLU_SILU || K == EPI_GLU_GELU || K == EPI_GELU;
+  const long t64 = (long)((p.M + 63) / 64) * ((p.N + 63) / 64);
+  if constexpr (kFragments)
     if (t64 <= 96) return launch_ring<32, 32, 8, 2, K>(p, e, s);
-    const long t96 = (long)((p.M + 63) / 64) * ((p.N + 95) / 96);
-    if (t64 > 512 && t96 <= 512) return launch_ring<64, 96, 4, 2, K>(p, e, s);
+  if (t64 > 512) {
+    if constexpr (kFragments) {
+      const long t96 = (long)((p.M + 63) / 64) * ((p.N + 95) / 96);
+      if (t96 <= 512 && !(TileLdsEpi<E>::value && p.K < 2048)) return launch_ring<64, 96, 4, 2, K>(p, e, s);
+    }
+    if (t64 > 768 || !(kUp || p.M <= 256)) return launch_bf16<64, 64, 2, 2, 2, 3, K>(p, e, s);
   }
   return launch_ring<64, 64, 3, 3, K>(p, e, s);
 }
@@ -535,18 +546,38 @@ hipError_t dispatch(DType dt, const GemmProblem& p, const EpiParams& e, hipStrea
     }
     return hipErrorInvalidValue;
   }
-  // tile choice by how many blocks each shape yields (256 CUs): GEMMs with many rows
-  // take 256 x 256 tiles on 8 waves (gemm_pingpong.h), mid-size ones 128 x 128 at two blocks per CU, and
-  // the narrow (N = d_model) projections 64 x 64 at three blocks per CU
-  const long t256 = (long)((p.M + 255) / 256) * ((p.N + 255) / 256);
-  const long t128 = (long)((p.M + 127) / 128) * ((p.N + 127) / 128);
-  if ((p.M >= 4096 || p.N >= 16384) && t256 >= 128 && pingpong_ok(p)) return launch_pp<K>(p, e, s);
+  // tile choice by how many blocks each shape yields (256 CUs) and the rounds they run in: 256 x
+  // 256 tiles hold 256 blocks at once (gemm_pingpong.h), 192 x 128 and 128 x 128 ones 512
+  const auto tiles = [&](int bm, int bn) { return (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
+  const long t256 = tiles(256, 256), t128 = tiles(128, 128);
+  const long r256 = (t256 + 255) / 256, r192 = (tiles(192, 128) + 511) / 512, r128 = (t128 + 511) / 512;
+  if ((p.M >= 4096 || p.N >= 16384) && t256 >= 128) {
+    // rounds times the time of one, 80 : 75 : 57 over K = 512 to 8 192 (by 256 x 256 / 192 x 128 / 128 x
+    // 128 tiles, us: GLU 4 600 x 4 096 x 768 40.3 / 28.3 / 34.2, 8 192 x 4 096 x 768 46.2 / 64.4 /
+    // 53.9; 6 144 x 3 072 x 2 048 110 / 75 / 88; residual 4 096 x 2 048 x 2 048 53 / 50 / 42, 32 768 x
+    // 2 048 x 8 192 818 / 1 272 / 1 083).  Two exceptions: where one round of 256 x 256 tiles holds a
+    // long K, 192 x 128 ones lose (5 000 x 2 048 x 8 192 162 : 189); and the staged q/k/v epilogue
+    // stands between two tiles of a block, too long beside a short K (12 288 x 2 304 x 768 63.9 / 55.1
+    // / 56.5, 16 384 rows 89.0 / 75.5 / 73.7).
+    constexpr long kNever = 1l << 40;
+    const long c256 = pingpong_ok(p) && !(TileLdsEpi<Epi<K, bf16>>::value && p.K < 2048) ? 80 * r256 : kNever;
+    const long c192 = r256 == 1 && p.K >= 4096 ? kNever : 75 * r192, c128 = 57 * r128;
+    if (c256 <= c192 && c256 <= c128) {
+      // float32 outputs of a short K and fewer than 4 096 rows: a block per tile, which leaves
+      // its stores behind when it ends, where the walking one waits for them before its next
+      // tile (1 280 x 32 768 x 768 111 -> 94 us, 2 048 rows 166 -> 147, 3 500 x 16 384 x 512 127 -> 110;
+      // from 4 600 rows on the other way round, 6 144 x 8 192 x 1 024 112 against 119)
+      if constexpr (K == EPI_STORE_F32)
+        if (p.K <= 1024 && p.M < 4096) return launch_bf16<256, 256, 2, 2, 4, 1, K>(p, e, s);
+      return launch_pp<K>(p, e, s);
+    }
+    if (c192 <= c128) return launch_bf16<192, 128, 2, 2, 2, 2, K>(p, e, s);
+    return launch_bf16<128, 128, 2, 2, 2, 2, K>(p, e, s);
+  }
   if (t128 >= 256) {
-    // two blocks per CU run in rounds of 512; 192 x 128 tiles win when they need fewer
-    // rounds for the same rows (e.g. 768 tiles of 128 x 128 = 1.5 rounds -> 512 of 192 x 128)
-    const long t192 = (long)((p.M + 191) / 192) * ((p.N + 127) / 128);
-    const long cost128 = (t128 + 511) / 512 * 128 * 128, cost192 = (t192 + 511) / 512 * 192 * 128;
-    if (cost192 < cost128) return launch_bf16<192, 128, 2, 2, 2, 2, K>(p, e, s);
+    // 192 x 128 tiles win when they need fewer rounds for the same rows (e.g. 768 tiles of 128 x
+    // 128 = 1.5 rounds -> 512 of 192 x 128)
+    if (r192 * 192 < r128 * 128) return launch_bf16<192, 128, 2, 2, 2, 2, K>(p, e, s);
     return launch_bf16<128, 128, 2, 2, 2, 2, K>(p, e, s);
   }
   return launch_small<K>(p, e, s);

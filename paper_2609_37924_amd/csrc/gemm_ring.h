@@ -6,10 +6,10 @@
 // share the tile.  64 x 64 tiles, against the two-buffer loop of gemm_bf16_kernel on the same
 // tiles (weights from HBM): 64 x 3 072 x 2 048 17.2 -> 12.2 us, 384 x 768 x 2 048 16.5 -> 12.1,
 // 384 x 4 096 x 768 9.0 -> 8.3, 1 024 x 2 048 x 2 048 18.6 -> 15.8; with more than two tiles per
-// CU the blocks hide each other's latency and both loops take the same time (3 072 x 768 x
-// 2 048: 20.5 us).  Also measured: fragments loaded straight into registers, the waves
-// splitting K (384 x 768 x 2 048 13.4 to 17.9 us: the loads touch 64 bytes a row), and eight
-// waves splitting every K tile (10.8 us there, but 23.5 at 3 072 rows).
+// CU the blocks hide each other's latency and the two-buffer loop is as fast or faster
+// (launch_small).  Also measured: fragments loaded straight into registers, the waves splitting
+// K (384 x 768 x 2 048 13.4 to 17.9 us: the loads touch 64 bytes a row), and eight waves splitting
+// every K tile (10.8 us there, but 23.5 at 3 072 rows).
 #pragma once
 #include "gemm_kernel.h"
 
@@ -184,6 +184,14 @@ hipError_t launch_ring(const GemmProblem& p0, const EpiParams& e, hipStream_t s)
   GemmProblem p = p0;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   if (!p.M_dev) xcd_regions(tiles_m, tiles_n, BM, BN, p.rm, p.rn);
+  if (BN == 96 && p.rm > 0) {
+    // two of these tiles per CU fill the chip: an XCD holds 64, and where its region is too long
+    // (an odd number of tile rows leaves 1 x 8 regions) a band streams fewer rows per K step
+    // (residual 3 500 x 768 x 768, regions of 55 x 1 tiles: 14.5 -> 12.2 us, x 2 048 24.0 -> 20.7; 3 072
+    // rows, regions of 6 x 8: 11.4 against 11.8)
+    const int wm = p.rm < 64 ? p.rm : 64, wn = (64 + wm - 1) / wm, h = xcd_band(tiles_m, BM, BN, 64);
+    if (wm * BM + (wn < p.rn ? wn : p.rn) * BN > h * BM + (64 + h - 1) / h * BN) p.rm = p.rn = 0;
+  }
   p.band = p.rm > 0 ? 0 : xcd_band(tiles_m, BM, BN, 32);
   const int blocks = p.band > 0 ? (tiles_m * tiles_n + 7) / 8 * 8 : tiles_m * tiles_n;
   launch_timed(gemm_ring_kernel<BM, BN, NS, MINB, K>, dim3(blocks, p.ksplit), dim3(256), 0, s, p, e);

@@ -3,8 +3,8 @@
 The vocabulary head of a model without layers is one product of known operands: its
 normalised input is read back (bf16, exact as float32) and the logits are compared with the
 float64 product of that input and the stored weights.  d_model 64 to 704 gives one
-to eleven K tiles; the row counts and vocabularies leave partial 256, 64 and 32-row tiles and
-grids with and without an even split over the chip's eight dies.
+to eleven K tiles; the row counts and vocabularies leave partial tiles of every size that the
+dispatch knows and grids with and without an even split over the chip's eight dies.
 """
 import pytest
 import torch
@@ -29,7 +29,14 @@ def _model(d, vocab, B, P, G, base="small", nan_rows=()):
 @pytest.mark.parametrize("d,vocab,B,G", [(128, 32768, 1, 257), (192, 33028, 1, 300), (320, 33028, 3, 100),
                                          (128, 16640, 2, 512), (192, 65540, 1, 63),
                                          (64, 300, 1, 63), (64, 516, 1, 1), (128, 1028, 1, 65), (320, 5000, 1, 129),
-                                         (704, 96, 2, 33), (640, 3000, 3, 100)])
+                                         (704, 96, 2, 33), (640, 3000, 3, 100),
+                                         # 256 x 256 tiles: one and two per block, two to eleven K tiles
+                                         (192, 3836, 4, 1025), (128, 6396, 4, 1250), (704, 6396, 4, 1250),
+                                         # the same tiles, a block each (short K, fewer than 4 096 rows)
+                                         (192, 32764, 2, 250), (128, 16388, 3, 1333),
+                                         # 192 x 128 tiles above and below 4 096 rows, 64 x 64 at three and more per CU, 64 x 96
+                                         (192, 2300, 4, 1030), (128, 9000, 2, 500), (192, 3900, 1, 900),
+                                         (320, 1028, 2, 1040)])
 def test_product_tiles(d, vocab, B, G):
     _head_product(*_model(d, vocab, B, 1, G), d, vocab, B, G)
 
