@@ -502,11 +502,12 @@ __global__ __launch_bounds__(256) void gemm_f32_large_kernel(GemmProblem p, EpiP
 //
 // More than 512 put three blocks on some CUs, which hide each other's latency:
 //  - 64 x 96 tiles where they are at most 512 (residual, fusion 2 and float32 outputs, q/k/v of a
-//    long K, whose strips then leave LDS out): no CU has more than two, which load 320 rows per K step instead of 384.  us, 64 x 64 on the two-buffer
-//    loop against 64 x 96: 3 072 x 768 x 2 048 21.2 : 19.9, 3 500 x 768 x 3 072 30.5 : 28.9, 1 272 x
-//    2 048 x 2 048 21.3 : 20.3, 640 x 4 608 x 4 096 52.7 : 44.8, 2 625 x 1 024 x 1 024 14.5 : 13.5, 3 000 x
-//    768 x 768 11.8 : 11.9; q/k/v 1 024 x 2 304 x 768 10.7 : 11.8, 1 024 x 3 072 x 2 048 21.7 : 21.3 (a
-//    refresh step of three such layers 1 270 : 1 260).
+//    long K, whose strips then leave LDS out): no CU has more than two, which load 320 rows per
+//    K step instead of 384.  us, 64 x 64 on the two-buffer loop against 64 x 96: 3 072 x 768 x 2 048
+//    21.2 : 19.9, 3 500 x 768 x 3 072 30.5 : 28.9, 1 272 x 2 048 x 2 048 21.3 : 20.3, 640 x 4 608 x
+//    4 096 52.7 : 44.8, 2 625 x 1 024 x 1 024 14.5 : 13.5, 3 000 x 768 x 768 11.8 : 11.9; q/k/v 1 024 x
+//    2 304 x 768 10.7 : 11.8, 1 024 x 3 072 x 2 048 21.7 : 21.3 (a refresh step of three such layers
+//    1 270 : 1 260).
 //  - else the two-buffer loop (gemm_kernel.h); us, it against the ring: 768 x 3 840 x 1 536 15.9 :
 //    17.5, 1 024 x 2 304 x 768 9.5 : 10.3, 300 x 10 240 x 4 096 55.2 : 61.4, fusion 1 900 x 3 840 x 1 536
 //    22.5 : 24.9, 1 800 x 2 048 x 8 192 110.8 : 143.2.  Up to 768 tiles the ring stays for the up
