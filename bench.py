@@ -236,7 +236,7 @@ def attach_counters(config, K, kernels):
 
 # ------------------------------------------------------------ profile render ---
 def short_name(n):
-    n = re.sub(r"\(tadm::GemmProblem, tadm::EpiParams\)", "", n)
+    n = re.sub(r"\(tadm::GemmProblem, tadm::EpiParams(, int)?\)", "", n)
     n = n.replace("void ", "").replace("tadm::(anonymous namespace)::", "")
     if "gemm" not in n:
         n = re.sub(r"\(.*$", "", n)
