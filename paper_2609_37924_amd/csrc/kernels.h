@@ -247,9 +247,10 @@ constexpr int ENTROPY_MAX_CANVAS = 8192;
 // (2^31 + 3, l, b, step).
 hipError_t corrupt_pair(const int32_t* x, int B, int L, const float* t, const float* ts, float eps, uint64_t seed,
                         uint32_t step, int mask_id, int32_t* zt, int32_t* zs, hipStream_t s);
-// ce[r] = logsumexp(logits[r]) - logits[r][x[idx[r]]] for the rows r < *count (grid max_rows).
-hipError_t masked_ce(const float* logits, int V, int max_rows, const int* count, const int32_t* idx, const int32_t* x,
-                     float* ce, hipStream_t s);
+// ce[r] = logsumexp(logits[r]) - logits[r][x[idx[r]]] for the rows r < *count (grid max_rows) of
+// V entries, ld apart (a multiple of 4).
+hipError_t masked_ce(const float* logits, int ld, int V, int max_rows, const int* count, const int32_t* idx,
+                     const int32_t* x, float* ce, hipStream_t s);
 // loss[b] = (1 / t_b) sum_{l masked} ce[row_map[b L + l]] (row_map -1: not masked); n_masked nullable.
 hipError_t weighted_loss(const float* ce, const int32_t* row_map, int B, int L, const float* t, float* loss,
                          int32_t* n_masked, hipStream_t s);

@@ -1725,19 +1725,20 @@ tadm_status tadm_train_loss(tadm_model* m, const int32_t* x_dev, int32_t B, int3
   HIPCHK(rms_norm_gather(m->dt, s.x, m->Wf(m->lay.final_norm), cf.rms_eps, s.cidx, s.count, N, L, L, 0, d, s.xn,
                          m->stream));
   TRY(prof_end(m, TADM_STAGE_DENOISE));
-  TRY(ensure_logits(m, (size_t)N * V));
+  const int ldl = (V + 3) & ~3;  // the head stores four features at a time
+  TRY(ensure_logits(m, (size_t)N * ldl));
   TRY(prof_begin(m, TADM_STAGE_HEAD));
   {
     GemmProblem p{N, V, d, s.xn, d, d, nullptr, 0, m->W(m->lay.w_out), d};
     p.M_dev = s.count;
     EpiParams e;
     e.out = s.logits;
-    e.ldo = V;
+    e.ldo = ldl;
     HIPCHK(gemm(m->dt, p, EPI_STORE_F32, e, m->stream));
   }
   TRY(prof_end(m, TADM_STAGE_HEAD));
   TRY(prof_begin(m, TADM_STAGE_SAMPLE));
-  HIPCHK(masked_ce(s.logits, V, N, s.count, s.cidx, x_dev, s.ce, m->stream));
+  HIPCHK(masked_ce(s.logits, ldl, V, N, s.count, s.cidx, x_dev, s.ce, m->stream));
   TRY(prof_end(m, TADM_STAGE_SAMPLE));
   TRY(prof_begin(m, TADM_STAGE_SELECT));
   HIPCHK(weighted_loss(s.ce, s.row_map, B, L, t_dev, loss_dev, n_masked_dev, m->stream));

@@ -41,33 +41,31 @@ __device__ __forceinline__ float exp_sum(float y) {
   return ldexpf(__builtin_amdgcn_exp2f(g), (int)n);
 }
 
-// grid max_rows, 256 threads: row r < *count of the compacted logits is canvas entry
-// idx[r]; ce[r] = log sum_v exp(l_v) - l_target, with a fixed reduction order.
-__global__ __launch_bounds__(256) void ce_kernel(const float* logits, int V, const int* count, const int32_t* idx,
-                                                 const int32_t* x, float* ce) {
+// grid max_rows, 256 threads: row r < *count of the compacted logits (ld entries apart, ld a
+// multiple of 4, V of them in use) is canvas entry idx[r]; ce[r] = log sum_v exp(l_v) -
+// l_target, with a fixed reduction order.
+__global__ __launch_bounds__(256) void ce_kernel(const float* logits, int ld, int V, const int* count,
+                                                 const int32_t* idx, const int32_t* x, float* ce) {
   __shared__ float red[4];
   const int r = blockIdx.x;
   if (r >= *count) return;
-  const float* lg = logits + (size_t)r * V;
+  const float* lg = logits + (size_t)r * ld;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // f(l_v, l_v+1, l_v+2, l_v+3) over the row, four float4 loads in flight per thread (a
-  // vocabulary that is not a multiple of four ends in single entries, padded with -inf)
-  const bool vec = (V & 3) == 0;
+  // f(l_v, l_v+1, l_v+2, l_v+3) over the row, four float4 loads in flight per thread, entries
+  // past V as -inf
   auto for_each = [&](auto f) {
     const int nq = (V + 3) / 4;
     for (int q0 = tid; q0 < nq; q0 += 4 * 256) {
       float4 x[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int q = q0 + 256 * u, v = 4 * q;
-        x[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-        if (vec && q < nq) {
-          x[u] = *reinterpret_cast<const float4*>(lg + v);
-        } else if (!vec) {
-          if (v < V) x[u].x = lg[v];
-          if (v + 1 < V) x[u].y = lg[v + 1];
-          if (v + 2 < V) x[u].z = lg[v + 2];
-          if (v + 3 < V) x[u].w = lg[v + 3];
+        const int q = q0 + 256 * u;
+        x[u] = q < nq ? *reinterpret_cast<const float4*>(lg + 4 * q)
+                      : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        if (4 * q + 3 >= V) {
+          x[u].w = -INFINITY;
+          if (4 * q + 2 >= V) x[u].z = -INFINITY;
+          if (4 * q + 1 >= V) x[u].y = -INFINITY;
         }
       }
 #pragma unroll
@@ -134,10 +132,11 @@ hipError_t corrupt_pair(const int32_t* x, int B, int L, const float* t, const fl
   return hipGetLastError();
 }
 
-hipError_t masked_ce(const float* logits, int V, int max_rows, const int* count, const int32_t* idx, const int32_t* x,
-                     float* ce, hipStream_t s) {
+hipError_t masked_ce(const float* logits, int ld, int V, int max_rows, const int* count, const int32_t* idx,
+                     const int32_t* x, float* ce, hipStream_t s) {
+  if (ld < V || ld % 4) return hipErrorInvalidValue;
   if (max_rows == 0) return hipSuccess;
-  launch_timed(ce_kernel, dim3(max_rows), dim3(256), 0, s, logits, V, count, idx, x, ce);
+  launch_timed(ce_kernel, dim3(max_rows), dim3(256), 0, s, logits, ld, V, count, idx, x, ce);
   return hipGetLastError();
 }
 

@@ -50,3 +50,14 @@ def test_train_loss_matches_oracle(name, overrides, B, L, rtol):
     assert np.all(np.abs(got - ref) <= rtol * np.abs(ref) + 1e-6), (got, ref)
     if B > 3:
         assert got[3] == 0.0
+
+
+@pytest.mark.parametrize("name,overrides,B,L,rtol", [
+    ("tiny", dict(vocab=257), 3, 24, 1e-4),
+    ("tiny", dict(vocab=1022), 3, 24, 1e-4),
+    ("small", dict(vocab=4099, n_anchor=1, n_denoise=1), 2, 64, 2e-2),
+])
+def test_train_loss_of_any_vocabulary(name, overrides, B, L, rtol):
+    """Vocabularies that are no multiple of four: the head stores four features at a time, so a
+    row of logits ends in one to three entries that belong to no token."""
+    test_train_loss_matches_oracle(name, overrides, B, L, rtol)
